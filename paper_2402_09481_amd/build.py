@@ -1,8 +1,8 @@
 """Build libextractor.so (gfx950) in-tree with hipcc.
 
 The transform kernel file is compiled as several parts in parallel (one per
-group of template instantiations), the Von Neumann kernels and the C-ABI as
-one object each, then linked with the C-ABI into one shared
+group of template instantiations), the GF(2)[t] kernels, the Von Neumann kernels
+and the C-ABI as one object each, then linked with the C-ABI into one shared
 library next to this file. Always rebuilds when called."""
 from __future__ import annotations
 
@@ -45,7 +45,7 @@ def build(verbose: bool = False) -> str:
     for part in range(NTT_PARTS):
         obj = os.path.join(BUILD, "ntt_part%d.o" % part)
         jobs.append(([HIPCC] + FLAGS + ["-DNTT_PART=%d" % part, "-c", os.path.join(CSRC, "ntt.hip"), "-o", obj], obj))
-    for src, extra in (("vonneumann.hip", VN_FLAGS), ("abi.cpp", [])):
+    for src, extra in (("vonneumann.hip", VN_FLAGS), ("gf2.hip", []), ("abi.cpp", [])):
         obj = os.path.join(BUILD, os.path.splitext(src)[0] + ".o")
         jobs.append(([HIPCC] + FLAGS + extra + ["-c", os.path.join(CSRC, src), "-o", obj], obj))
     workers = min(len(jobs), max(1, (os.cpu_count() or 2)))

@@ -17,6 +17,7 @@
 #include <vector>
 
 #include "field.h"
+#include "gf2.h"
 #include "kernels.h"
 
 using namespace ext;
@@ -506,6 +507,10 @@ struct ext_ctx {
     // plans for single extraction calls where they differ (the GPU mostly idle
     // during one job: fewer, larger workgroups can be faster); same key
     std::map<int, Plan> tuned_single;
+    // size classes (same key) whose plan the caller set on this context: their
+    // extractions run the number-theoretic transform of that plan
+    std::map<int, int> chosen;
+    bool gf2 = true;  // the GF(2)[t] path (off where a testing aid forces a transform)
     // pinned status words for EXT_SYNC calls without a status pointer
     std::vector<int32_t *> pinned_status;
     // batch graph cache
@@ -516,9 +521,8 @@ struct ext_ctx {
     // for `replayed`, recorded after each replay, on the device).
     struct GraphEntry {
         hipGraphExec_t exec = nullptr;
-        JobDev *desc_dev = nullptr;
-        JobDev *desc_host[2] = {nullptr, nullptr};  // pinned
-        size_t ndesc = 0;
+        char *desc_dev = nullptr;
+        char *desc_host[2] = {nullptr, nullptr};  // pinned
         hipEvent_t done[2] = {nullptr, nullptr};
         bool used[2] = {false, false};
         int next = 0;
@@ -694,6 +698,127 @@ int plan_shape(ext_ctx *c, const Shape &s, Plan &p, uint32_t flags = 0, bool bat
 }  // namespace
 
 namespace {
+
+// ------------------------------------------------------------------ the GF(2)[t] path
+
+// Rows, groups and workspace of a shape on the GF(2)[t] path (gf2.h: Gf2Job).
+struct Gf2Plan {
+    uint32_t px = 0, ps = 0, pz = 0, splits = 1;
+    uint32_t rows_lg = 0, hx = 0, hz = 0, nx = 0, nz = 0;
+    size_t x = 0, s = 0, g = 0, xb = 0, sb = 0, flags = 0, total = 0;
+};
+
+// Product rows computed term by term cost px pz row products; a transform over rows costs
+// about as much as GF2_DIRECT_MAX of them at these sizes.
+constexpr uint64_t GF2_DIRECT_MAX = 12288;
+
+// jobs: how many extractions share the launch.
+Gf2Plan gf2_plan(const Shape &s, size_t jobs = 1) {
+    const uint64_t B = gf2::BLOCK_BITS;
+    Gf2Plan p;
+    p.px = (uint32_t)((conv_n(s) + B - 1) / B);
+    p.pz = (uint32_t)((s.m + B - 1) / B);
+    p.ps = p.px + p.pz - 1;
+    const size_t row = gf2::ROW_WORDS * 4;
+    size_t groups = 0;
+    if ((uint64_t)p.px * p.pz <= GF2_DIRECT_MAX) {
+        // product rows: eight waves each, split further while fewer than 1024 waves run, and
+        // so that no wave sums more than 32 products where others would wait for it
+        const uint32_t fill = (uint32_t)(128 / std::min<size_t>(jobs, 128)), most = (p.px + 7) / 8;
+        const uint32_t want = std::max((fill + p.pz - 1) / p.pz, (p.px + 255) / 256);
+        p.splits = std::max<uint32_t>(1, std::min<uint32_t>({want, most, 32}));
+    } else {
+        const uint32_t top = 1u << gf2::ROWS_LG_MAX;
+        if (p.ps <= top) {
+            p.rows_lg = (uint32_t)std::max(gf2::ROWS_LG_MIN, ceil_log2(p.ps));
+            p.hx = p.px;
+            p.hz = p.pz;
+            p.nx = p.nz = 1;
+        } else {
+            p.rows_lg = gf2::ROWS_LG_MAX;
+            if (p.pz <= top / 2) {
+                p.nz = 1;
+                p.hz = p.pz;
+                p.nx = (p.px + top - p.hz) / (top - p.hz + 1);
+                p.hx = (p.px + p.nx - 1) / p.nx;
+            } else {
+                p.hx = p.hz = top / 2;
+                p.nx = (p.px + p.hx - 1) / p.hx;
+                p.nz = (p.pz + p.hz - 1) / p.hz;
+            }
+        }
+        groups = row << p.rows_lg;
+    }
+    p.s = p.px * row;
+    p.g = p.s + p.ps * row;
+    p.xb = p.g + (size_t)p.splits * p.pz * row;
+    p.sb = p.xb + p.nx * groups;
+    p.flags = p.sb + (groups ? p.nx + p.nz - 1 : 0) * groups;
+    p.total = p.flags + 256;
+    return p;
+}
+
+// A single call on the GF(2)[t] path is three or four launches of one or two waves' latency
+// each, about 42 us from 2^15 to 2^20 (MI355X, back to back), where the transform takes
+// 26 us at 2^15, 32 us at 2^19 and 58 us at 2^21. Batch members share the launches, so
+// that only their work counts.
+constexpr uint64_t GF2_SINGLE_MIN = uint64_t(1) << 20;
+
+// Whether an extraction runs on the GF(2)[t] path: wherever its workspace is no larger than
+// the number-theoretic transform's (shapes beyond about 2^35 bits keep the latter, whose
+// pieces share one workspace), unless the caller asks for one transform, for a cached
+// seed spectrum, or has set the plan of this size class on this context.
+bool gf2_route(ext_ctx *c, const Shape &s, uint32_t flags, bool single) {
+    if (!c->gf2 || (flags & (EXT_SINGLE_TRANSFORM | EXT_SEED_CACHED))) return false;
+    if (s.Lmin <= (single ? GF2_SINGLE_MIN : uint64_t(1) << max_small_lg())) return false;
+    Plan p;
+    if (make_plan(s.Lmin, 0, p) == EXT_OK) {
+        std::lock_guard<std::mutex> g(c->mu);
+        auto it = c->chosen.find(p.field * 64 + p.lg);
+        if (it != c->chosen.end() && (it->second & (single ? 3 : 1))) return false;
+    }
+    if (plan_shape(c, s, p, flags, !single) != EXT_OK) return false;
+    return s.n <= (uint64_t(1) << 36) && gf2_plan(s).total <= workspace_layout(p).total;
+}
+
+Gf2Job gf2_job(const Shape &s, const Gf2Plan &p, const uint64_t *x, const uint64_t *y, uint64_t *z, int32_t *status,
+               uint32_t flags, char *ws) {
+    Gf2Job j;
+    std::memset(&j, 0, sizeof(j));
+    const uint64_t n = conv_n(s), N = n + s.m - 1;
+    if (s.kind == EXT_KIND_TOEPLITZ) {
+        j.ex = Emb{x, n, 0, 0, 0, 0, EMB_PREFIX, 0};
+        j.ey = Emb{y, N, n - 1, N, (flags & EXT_SEED_LINEAR) ? 0 : s.m % N, N, EMB_SEED, 0};
+    } else {
+        j.ex = Emb{x, s.n, n, n, 0, 0, EMB_REV, 0};
+        j.ey = Emb{y, n, n - 1, N, 0, n, EMB_SEED, 0};
+        j.degen_n = s.kind == EXT_KIND_DODIS ? s.n : 0;
+    }
+    j.X = (uint32_t *)(ws + p.x);
+    j.S = (uint32_t *)(ws + p.s);
+    j.G = (uint32_t *)(ws + p.g);
+    j.XB = (uint32_t *)(ws + p.xb);
+    j.SB = (uint32_t *)(ws + p.sb);
+    j.flags = (uint32_t *)(ws + p.flags);
+    j.z = z;
+    j.status = status;
+    j.n = n;
+    j.m = s.m;
+    j.px = p.px;
+    j.ps = p.ps;
+    j.pz = p.pz;
+    j.splits = p.splits;
+    j.rows_lg = p.rows_lg;
+    j.hx = p.hx;
+    j.hz = p.hz;
+    j.nx = p.nx;
+    j.nz = p.nz;
+    // direct: a row's slices together; for a transform over rows: a slice's rows together
+    j.rs = p.rows_lg ? 16 : gf2::ROW_WORDS;
+    j.x_ss = p.rows_lg ? uint64_t(16) * p.px : 16;
+    j.s_ss = p.rows_lg ? uint64_t(16) * p.ps : 16;
+    return j;
+}
 
 struct Lease {
     char *ptr = nullptr;
@@ -944,6 +1069,33 @@ hipError_t enqueue(ext_ctx *c, const Plan &p, uint32_t njobs, const JobDev *jobs
     return e;
 }
 
+// The launches of one extraction on the GF(2)[t] path.
+hipError_t enqueue_gf2(ext_ctx *c, const Gf2Job &j, hipStream_t s, bool quiet) {
+    Tracer tr(c, s, quiet);
+    tr.begin();
+    hipError_t e = launch_gf2_fwd(gf2_fwd_workgroups(j), nullptr, j, nullptr, s);
+    if (tr.on) tr.end("gf2_fwd");
+    if (e != hipSuccess) return e;
+    if (j.rows_lg) {
+        tr.begin();
+        e = launch_gf2_rows_fwd((int)j.rows_lg, gf2_rows_fwd_workgroups(j), nullptr, j, nullptr, s);
+        if (tr.on) tr.end("gf2_rows_fwd");
+        if (e != hipSuccess) return e;
+        tr.begin();
+        e = launch_gf2_rows_inv((int)j.rows_lg, gf2_rows_inv_workgroups(j), nullptr, j, nullptr, s);
+        if (tr.on) tr.end("gf2_rows_inv");
+    } else {
+        tr.begin();
+        e = launch_gf2_mul(gf2_mul_workgroups(j), nullptr, j, nullptr, s);
+        if (tr.on) tr.end("gf2_mul");
+    }
+    if (e != hipSuccess) return e;
+    tr.begin();
+    e = launch_gf2_inv(gf2_inv_workgroups(j), nullptr, j, nullptr, s);
+    if (tr.on) tr.end("gf2_inv");
+    return e;
+}
+
 int32_t *take_pinned_status(ext_ctx *c) {
     std::lock_guard<std::mutex> g(c->mu);
     if (!c->pinned_status.empty()) {
@@ -1038,6 +1190,38 @@ ext_ctx::SeedEntry *seed_entry(ext_ctx *c, const Shape &sh, const Plan &p, const
     return ent;
 }
 
+// The launches of one extraction by number-theoretic transform (workspace ws).
+hipError_t enqueue_transform(ext_ctx *c, const Shape &sh, const Plan &p, const uint64_t *x, const uint64_t *y,
+                             uint64_t *z, int32_t *st, uint32_t flags, char *ws, hipStream_t s) {
+    JobDev jd = make_jobdev(sh, p, x, y, z, st, flags, ws);
+    hipError_t e = hipSuccess;
+    // (the two-piece schedule does not use the seed cache)
+    ext_ctx::SeedEntry *se = (flags & EXT_SEED_CACHED) && !p.small && p.pieces == 1
+                                 ? seed_entry(c, sh, p, y, flags, s, jd, e)
+                                 : nullptr;
+    if (se && e != hipSuccess) {
+        std::lock_guard<std::mutex> g(c->mu);
+        se->busy--;
+    }
+    if (e != hipSuccess) return e;
+    if (se) {
+        jd.S = se->ptr;
+        e = enqueue(c, p, 1, nullptr, &jd, sh.m, jd.degen_n != 0, s, false, PH_WARM);
+        if (e == hipSuccess) e = hipEventRecord(se->used, s);
+        std::lock_guard<std::mutex> g(c->mu);
+        se->busy--;
+        return e;
+    }
+    if (p.pieces < 2) return enqueue(c, p, 1, nullptr, &jd, sh.m, jd.degen_n != 0, s);
+    // the last piece's product, then each earlier piece's product plus the sum
+    // so far, then the first piece fused with that sum, one inverse, parity
+    for (int q = p.pieces - 1; q >= 1 && e == hipSuccess; --q) {
+        const JobDev jq = make_jobdev(sh, p, x, y, z, st, flags, ws, q);
+        e = enqueue(c, p, 1, nullptr, &jq, sh.m, false, s, false, q == p.pieces - 1 ? PH_FWD_BOTH : PH_FWD_ACC);
+    }
+    return e == hipSuccess ? enqueue(c, p, 1, nullptr, &jd, sh.m, jd.degen_n != 0, s, false, PH_TWO) : e;
+}
+
 int extract_one(ext_ctx *c, int kind, const uint64_t *x, uint64_t n, const uint64_t *y, uint64_t m, uint64_t *z,
                 uint32_t flags, int32_t *status, hipStream_t s) {
     if (!c) return EXT_EINVAL;
@@ -1045,12 +1229,14 @@ int extract_one(ext_ctx *c, int kind, const uint64_t *x, uint64_t n, const uint6
     int rc = shape_of(kind, n, m, sh);
     if (rc) return rc;
     if ((rc = validate(sh, x, y, z, flags)) != EXT_OK) return rc;
+    const bool gf2 = gf2_route(c, sh, flags, true);
     Plan p;
-    if ((rc = plan_shape(c, sh, p, flags)) != EXT_OK) return rc;
+    Gf2Plan gp;
+    if (gf2) gp = gf2_plan(sh);
+    else if ((rc = plan_shape(c, sh, p, flags)) != EXT_OK) return rc;
     if (hipSetDevice(c->device) != hipSuccess) return EXT_EDEVICE;
-    const Layout lay = workspace_layout(p);
     Lease lease;
-    if ((rc = pool_acquire(c, lay.total, s, lease)) != EXT_OK) return rc;
+    if ((rc = pool_acquire(c, gf2 ? gp.total : workspace_layout(p).total, s, lease)) != EXT_OK) return rc;
     int32_t *st = status;
     int32_t *mine = nullptr;
     if ((flags & EXT_SYNC) && !st) {
@@ -1062,36 +1248,8 @@ int extract_one(ext_ctx *c, int kind, const uint64_t *x, uint64_t n, const uint6
         *mine = 0;
         st = mine;
     }
-    JobDev jd = make_jobdev(sh, p, x, y, z, st, flags, lease.ptr);
-    hipError_t e = hipSuccess;
-    // (the two-piece schedule does not use the seed cache)
-    ext_ctx::SeedEntry *se = (flags & EXT_SEED_CACHED) && !p.small && p.pieces == 1
-                                 ? seed_entry(c, sh, p, y, flags, s, jd, e)
-                                 : nullptr;
-    if (se && e != hipSuccess) {
-        std::lock_guard<std::mutex> g(c->mu);
-        se->busy--;
-    }
-    if (e == hipSuccess) {
-        if (se) {
-            jd.S = se->ptr;
-            e = enqueue(c, p, 1, nullptr, &jd, sh.m, jd.degen_n != 0, s, false, PH_WARM);
-            if (e == hipSuccess) e = hipEventRecord(se->used, s);
-            std::lock_guard<std::mutex> g(c->mu);
-            se->busy--;
-        } else if (p.pieces >= 2) {
-            // the last piece's product, then each earlier piece's product plus the sum
-            // so far, then the first piece fused with that sum, one inverse, parity
-            for (int q = p.pieces - 1; q >= 1 && e == hipSuccess; --q) {
-                const JobDev jq = make_jobdev(sh, p, x, y, z, st, flags, lease.ptr, q);
-                e = enqueue(c, p, 1, nullptr, &jq, sh.m, false, s, false,
-                            q == p.pieces - 1 ? PH_FWD_BOTH : PH_FWD_ACC);
-            }
-            if (e == hipSuccess) e = enqueue(c, p, 1, nullptr, &jd, sh.m, jd.degen_n != 0, s, false, PH_TWO);
-        } else {
-            e = enqueue(c, p, 1, nullptr, &jd, sh.m, jd.degen_n != 0, s);
-        }
-    }
+    const hipError_t e = gf2 ? enqueue_gf2(c, gf2_job(sh, gp, x, y, z, st, flags, lease.ptr), s, false)
+                             : enqueue_transform(c, sh, p, x, y, z, st, flags, lease.ptr, s);
     pool_release(c, lease, s);
     if (e != hipSuccess) {
         if (mine) give_pinned_status(c, mine);
@@ -1114,6 +1272,7 @@ int extract_one(ext_ctx *c, int kind, const uint64_t *x, uint64_t n, const uint6
 
 namespace {
 void pinned_release_all(ext_ctx *c);
+int tune_set_in(ext_ctx *c, bool single, int word_bits, int lg, int nlev, const int *lgr, bool caller = true);
 
 void graph_entry_free(ext_ctx::GraphEntry &ge) {
     if (ge.exec) hipGraphExecDestroy(ge.exec);
@@ -1245,6 +1404,8 @@ int ext_create(ext_ctx **out, int hip_device, size_t hbm_budget_bytes, const cha
     c->batch_split_min_lg = BATCH_SPLIT_MIN_LG;
     if (const char *v = getenv("EXT_SPLIT_MIN_LG")) c->split_min_lg = atoi(v);
     if (const char *v = getenv("EXT_BATCH_SPLIT_MIN_LG")) c->batch_split_min_lg = atoi(v);
+    // (a context that a testing aid shapes runs the transform it asks for)
+    c->gf2 = !ff && !c->piece_bits && !getenv("EXT_SPLIT_MIN_LG") && !getenv("EXT_BATCH_SPLIT_MIN_LG");
     // twiddle tables
     auto upload = [&](int f, int k, const void *src, size_t bytes) -> bool {
         void *d = nullptr;
@@ -1304,10 +1465,7 @@ int ext_create(ext_ctx **out, int hip_device, size_t hbm_budget_bytes, const cha
                 int k = sscanf(line + (single ? 7 : 0), "%d %d %d %d %d %d %d", &wb, &lg, &nlev, &r[0], &r[1], &r[2],
                                &r[3]);
                 if (k >= 3 && k == 3 + std::max(nlev, 0)) {
-                    if (single)
-                        ext_tune_set_single(c, wb, lg, nlev, r);
-                    else
-                        ext_tune_set(c, wb, lg, nlev, r);
+                    tune_set_in(c, single, wb, lg, nlev, r, /*caller=*/false);
                 }
             }
             fclose(f);
@@ -1341,7 +1499,7 @@ void ext_destroy(ext_ctx *c) {
 
 namespace {
 
-int tune_set_in(ext_ctx *c, bool single, int word_bits, int lg, int nlev, const int *lgr) {
+int tune_set_in(ext_ctx *c, bool single, int word_bits, int lg, int nlev, const int *lgr, bool caller) {
     if (!c || (word_bits != 32 && word_bits != 64) || lg < MIN_LG || lg > 32) return EXT_EINVAL;
     const int field = tune_field(word_bits, lg);
     if (field < 0) return EXT_EINVAL;
@@ -1349,6 +1507,7 @@ int tune_set_in(ext_ctx *c, bool single, int word_bits, int lg, int nlev, const 
     std::map<int, Plan> &table = single ? c->tuned_single : c->tuned;
     if (nlev < 0) {
         table.erase(field * 64 + lg);
+        c->chosen[field * 64 + lg] &= single ? ~2 : ~1;
         return EXT_OK;
     }
     Plan p;
@@ -1362,6 +1521,7 @@ int tune_set_in(ext_ctx *c, bool single, int word_bits, int lg, int nlev, const 
     }
     if (!valid_plan(p)) return EXT_EINVAL;
     table[field * 64 + lg] = p;
+    if (caller) c->chosen[field * 64 + lg] |= single ? 2 : 1;
     return EXT_OK;
 }
 
@@ -1514,11 +1674,18 @@ int extract_toeplitz_noalloc(ext_ctx *c, const uint64_t *x, uint64_t n, const ui
     int32_t *st = status;
     const bool own_status = (flags & EXT_SYNC) && !st;
     if (own_status) st = (int32_t *)(ws + status_off);
-    JobDev jd = make_jobdev(sh, p, x, y, z, st, flags, p.small ? nullptr : ws);
-    // every workspace region is written before it is read (embedded bits, both
+    // every workspace region is written before it is read (embedded bits or rows, both
     // arrays, the parity string), so nothing needs clearing; launches are not
-    // traced (tracing creates events)
-    if (enqueue(c, p, 1, nullptr, &jd, sh.m, false, s, /*quiet=*/true) != hipSuccess) return EXT_EDEVICE;
+    // traced (tracing creates events). The GF(2)[t] path's workspace is no larger than
+    // the transform's, which fits.
+    hipError_t e;
+    if (gf2_route(c, sh, flags, true)) {
+        e = enqueue_gf2(c, gf2_job(sh, gf2_plan(sh), x, y, z, st, flags, ws), s, /*quiet=*/true);
+    } else {
+        JobDev jd = make_jobdev(sh, p, x, y, z, st, flags, p.small ? nullptr : ws);
+        e = enqueue(c, p, 1, nullptr, &jd, sh.m, false, s, /*quiet=*/true);
+    }
+    if (e != hipSuccess) return EXT_EDEVICE;
     if (!(flags & EXT_SYNC)) return EXT_OK;
     if (hipStreamSynchronize(s) != hipSuccess) return EXT_EDEVICE;
     int32_t v = 0;
@@ -1650,7 +1817,9 @@ namespace {
 struct Member {
     size_t job;
     Shape shape;
-    Plan plan;
+    Plan plan;        // transform members
+    bool gf2 = false;
+    Gf2Plan gp;       // GF(2)[t] members
 };
 
 // (a piece schedule's split is per job: it lives in the job's descriptors, so
@@ -1681,14 +1850,79 @@ struct BatchLayout {
         size_t ws_each;
     };
     std::vector<Chunk> chunks;
+    // GF(2)[t] members: chunks of jobs of any size whose workspaces fit the region
+    // together, each chunk one launch per step (the transforms over rows one per row
+    // count). `tab` names every workgroup's job (within the chunk) and its number in it.
+    std::vector<const Member *> gf2;
+    struct Gf2Launch {
+        uint32_t wgs = 0;
+        size_t tab = 0;  // first entry
+    };
+    struct Gf2Chunk {
+        size_t first, n;
+        Gf2Launch fwd, mul, inv, rows_fwd[gf2::ROWS_LG_MAX + 1], rows_inv[gf2::ROWS_LG_MAX + 1];
+    };
+    std::vector<Gf2Chunk> gf2_chunks;
+    size_t ntab = 0;
     size_t max_ws = 0;
     std::string sig;
+    // the staged block: the transforms' descriptors, the GF(2)[t] jobs, the tables
+    size_t gf2_offset() const { return align256(ndesc * sizeof(JobDev)); }
+    size_t tab_offset() const { return gf2_offset() + align256(gf2.size() * sizeof(Gf2Job)); }
+    size_t staged_bytes() const { return tab_offset() + ntab * sizeof(uint2); }
 };
+
+void layout_gf2(const std::vector<Member> &members, size_t cap, BatchLayout &bl) {
+    for (auto &mb : members)
+        if (mb.gf2) bl.gf2.push_back(&mb);
+    // the longest workgroups of the products first
+    std::stable_sort(bl.gf2.begin(), bl.gf2.end(), [](const Member *a, const Member *b) { return a->gp.px > b->gp.px; });
+    for (size_t i = 0; i < bl.gf2.size();) {
+        BatchLayout::Gf2Chunk ch{};
+        ch.first = i;
+        size_t ws = 0;
+        auto add = [](BatchLayout::Gf2Launch &l, uint32_t wgs) { l.wgs += wgs; };
+        for (; i < bl.gf2.size() && (i == ch.first || ws + bl.gf2[i]->gp.total <= cap); ++i) {
+            const Member &mb = *bl.gf2[i];
+            ws += align256(mb.gp.total);
+            const Gf2Job j = gf2_job(mb.shape, mb.gp, nullptr, nullptr, nullptr, nullptr, 0, nullptr);
+            add(ch.fwd, gf2_fwd_workgroups(j));
+            if (j.rows_lg) {
+                add(ch.rows_fwd[j.rows_lg], gf2_rows_fwd_workgroups(j));
+                add(ch.rows_inv[j.rows_lg], gf2_rows_inv_workgroups(j));
+            } else {
+                add(ch.mul, gf2_mul_workgroups(j));
+            }
+            add(ch.inv, gf2_inv_workgroups(j));
+        }
+        ch.n = i - ch.first;
+        bl.max_ws = std::max(bl.max_ws, ws);
+        char b[96];
+        snprintf(b, sizeof b, "g%zu:%u:%u:%u", ch.n, ch.fwd.wgs, ch.mul.wgs, ch.inv.wgs);
+        bl.sig += b;
+        auto place = [&](BatchLayout::Gf2Launch &l) {
+            l.tab = bl.ntab;
+            bl.ntab += l.wgs;
+        };
+        place(ch.fwd);
+        place(ch.mul);
+        place(ch.inv);
+        for (int p = gf2::ROWS_LG_MIN; p <= gf2::ROWS_LG_MAX; ++p) {
+            place(ch.rows_fwd[p]);
+            place(ch.rows_inv[p]);
+            snprintf(b, sizeof b, ":%u", ch.rows_fwd[p].wgs);
+            bl.sig += b;
+        }
+        bl.sig += "|";
+        bl.gf2_chunks.push_back(ch);
+    }
+}
 
 void layout_batch(ext_ctx *c, const std::vector<Member> &members, BatchLayout &bl) {
     std::vector<const Member *> small;
     std::map<std::string, std::vector<const Member *>> large;
     for (auto &mb : members) {
+        if (mb.gf2) continue;
         if (mb.plan.small)
             small.push_back(&mb);
         else
@@ -1747,9 +1981,40 @@ void layout_batch(ext_ctx *c, const std::vector<Member> &members, BatchLayout &b
             bl.sig += b;
         }
     }
+    layout_gf2(members, cap, bl);
 }
 
-void fill_descs(const BatchLayout &bl, const ext_job *jobs, char *ws, JobDev *out) {
+void fill_descs(const BatchLayout &bl, const ext_job *jobs, char *ws, char *staged) {
+    JobDev *const out = (JobDev *)staged;
+    Gf2Job *const gout = (Gf2Job *)(staged + bl.gf2_offset());
+    uint2 *const tab = (uint2 *)(staged + bl.tab_offset());
+    for (auto &ch : bl.gf2_chunks) {
+        size_t off = 0, fwd = ch.fwd.tab, mul = ch.mul.tab, inv = ch.inv.tab;
+        size_t rf[gf2::ROWS_LG_MAX + 1], ri[gf2::ROWS_LG_MAX + 1];
+        for (int p = 0; p <= gf2::ROWS_LG_MAX; ++p) {
+            rf[p] = ch.rows_fwd[p].tab;
+            ri[p] = ch.rows_inv[p].tab;
+        }
+        for (uint32_t k = 0; k < ch.n; ++k) {
+            const Member &mb = *bl.gf2[ch.first + k];
+            const ext_job &j = jobs[mb.job];
+            const Gf2Job d =
+                gf2_job(mb.shape, mb.gp, j.x, j.y, j.z, j.status, j.flags & EXT_SEED_LINEAR, ws + off);
+            off += align256(mb.gp.total);
+            gout[ch.first + k] = d;
+            auto put = [&](size_t &at, uint32_t wgs) {
+                for (uint32_t w = 0; w < wgs; ++w) tab[at++] = make_uint2(k, w);
+            };
+            put(fwd, gf2_fwd_workgroups(d));
+            if (d.rows_lg) {
+                put(rf[d.rows_lg], gf2_rows_fwd_workgroups(d));
+                put(ri[d.rows_lg], gf2_rows_inv_workgroups(d));
+            } else {
+                put(mul, gf2_mul_workgroups(d));
+            }
+            put(inv, gf2_inv_workgroups(d));
+        }
+    }
     for (size_t i = 0; i < bl.n_small; ++i) {
         const Member &mb = *bl.order[i];
         const ext_job &j = jobs[mb.job];
@@ -1765,9 +2030,30 @@ void fill_descs(const BatchLayout &bl, const ext_job *jobs, char *ws, JobDev *ou
             }
 }
 
-hipError_t enqueue_batch(ext_ctx *c, const BatchLayout &bl, JobDev *desc_dev, uint32_t *counter, hipStream_t s,
+hipError_t enqueue_batch(ext_ctx *c, const BatchLayout &bl, char *staged_dev, uint32_t *counter, hipStream_t s,
                          bool quiet) {
+    JobDev *const desc_dev = (JobDev *)staged_dev;
     hipError_t e = hipSuccess;
+    for (auto &ch : bl.gf2_chunks) {
+        const Gf2Job none{};
+        const Gf2Job *const jobs = (const Gf2Job *)(staged_dev + bl.gf2_offset()) + ch.first;
+        const uint2 *const tab = (const uint2 *)(staged_dev + bl.tab_offset());
+        Tracer tr(c, s, quiet);
+        auto step = [&](const char *label, const BatchLayout::Gf2Launch &l, auto &&launch) {
+            if (e != hipSuccess || !l.wgs) return;
+            tr.begin();
+            e = launch(l.wgs, jobs, none, tab + l.tab);
+            if (tr.on) tr.end(label);
+        };
+        step("gf2_fwd", ch.fwd, [&](auto... a) { return launch_gf2_fwd(a..., s); });
+        step("gf2_mul", ch.mul, [&](auto... a) { return launch_gf2_mul(a..., s); });
+        for (int p = gf2::ROWS_LG_MAX; p >= gf2::ROWS_LG_MIN; --p) {
+            step("gf2_rows_fwd", ch.rows_fwd[p], [&](auto... a) { return launch_gf2_rows_fwd(p, a..., s); });
+            step("gf2_rows_inv", ch.rows_inv[p], [&](auto... a) { return launch_gf2_rows_inv(p, a..., s); });
+        }
+        step("gf2_inv", ch.inv, [&](auto... a) { return launch_gf2_inv(a..., s); });
+        if (e != hipSuccess) return e;
+    }
     if (bl.cls.total_items) {
         int cus = 0;
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess) cus = 256;
@@ -1881,7 +2167,8 @@ extern "C" int extract_batch(ext_ctx *c, ext_job *jobs, size_t count, uint32_t f
         if (rc == EXT_OK && (j.flags & ~(EXT_SEED_LINEAR | EXT_SYNC | EXT_SINGLE_TRANSFORM))) rc = EXT_EINVAL;
         if (rc == EXT_OK && j.kind != EXT_KIND_TOEPLITZ && (j.flags & EXT_SEED_LINEAR)) rc = EXT_EINVAL;
         if (rc == EXT_OK) rc = validate(mb.shape, j.x, j.y, j.z, j.flags & EXT_SEED_LINEAR);
-        if (rc == EXT_OK) rc = plan_shape(c, mb.shape, mb.plan, j.flags, true);  // piece schedules included
+        if (rc == EXT_OK && (mb.gf2 = gf2_route(c, mb.shape, j.flags, false))) mb.gp = gf2_plan(mb.shape, count);
+        else if (rc == EXT_OK) rc = plan_shape(c, mb.shape, mb.plan, j.flags, true);  // piece schedules included
         j.err = rc;
         if (rc != EXT_OK) {
             if (first == EXT_OK) first = rc;
@@ -1892,8 +2179,7 @@ extern "C" int extract_batch(ext_ctx *c, ext_job *jobs, size_t count, uint32_t f
     if (members.empty()) return first;
     BatchLayout bl;
     layout_batch(c, members, bl);
-    const size_t ndesc = bl.ndesc;
-    const size_t desc_bytes = align256(ndesc * sizeof(JobDev));
+    const size_t staged = bl.staged_bytes(), desc_bytes = align256(staged);
     hipError_t e = hipSuccess;
     if (flags & EXT_GRAPH) {
         std::lock_guard<std::mutex> graph_lock(c->graph_mu);
@@ -1916,7 +2202,6 @@ extern "C" int extract_batch(ext_ctx *c, ext_job *jobs, size_t count, uint32_t f
             ge = &c->graphs[bl.sig];
         }
         if (!ge->desc_dev) {
-            ge->ndesc = ndesc;
             bool ok = hipMalloc((void **)&ge->desc_dev, desc_bytes + 256) == hipSuccess &&
                       hipEventCreateWithFlags(&ge->replayed, hipEventDisableTiming) == hipSuccess;
             for (int k = 0; k < 2 && ok; ++k)
@@ -1927,7 +2212,7 @@ extern "C" int extract_batch(ext_ctx *c, ext_job *jobs, size_t count, uint32_t f
                 return EXT_EDEVICE;
             }
         }
-        uint32_t *counter = (uint32_t *)((char *)ge->desc_dev + desc_bytes);
+        uint32_t *counter = (uint32_t *)(ge->desc_dev + desc_bytes);
         // this staging buffer may still be read by the copy of the replay before last
         const int k = ge->next;
         ge->next ^= 1;
@@ -1935,7 +2220,7 @@ extern "C" int extract_batch(ext_ctx *c, ext_job *jobs, size_t count, uint32_t f
         fill_descs(bl, jobs, lease.ptr, ge->desc_host[k]);
         if (ge->ever) e = hipStreamWaitEvent(stream, ge->replayed, 0);  // the last replay read desc_dev
         if (e == hipSuccess)
-            e = hipMemcpyAsync(ge->desc_dev, ge->desc_host[k], ndesc * sizeof(JobDev), hipMemcpyHostToDevice, stream);
+            e = hipMemcpyAsync(ge->desc_dev, ge->desc_host[k], staged, hipMemcpyHostToDevice, stream);
         if (e == hipSuccess) e = hipEventRecord(ge->done[k], stream);
         ge->used[k] = true;
         if (e == hipSuccess && !ge->exec) {
@@ -1965,15 +2250,15 @@ extern "C" int extract_batch(ext_ctx *c, ext_job *jobs, size_t count, uint32_t f
         int rc = pool_acquire(c, desc_bytes + 256 + bl.max_ws, stream, lease);
         if (rc != EXT_OK) return rc;
         Pinned pin;
-        JobDev *host = (JobDev *)pinned_take(c, ndesc * sizeof(JobDev), pin);
+        char *host = pinned_take(c, staged, pin);
         if (!host) {
             pool_release(c, lease, stream);
             return EXT_EDEVICE;
         }
-        JobDev *desc_dev = (JobDev *)lease.ptr;
+        char *desc_dev = lease.ptr;
         uint32_t *counter = (uint32_t *)(lease.ptr + desc_bytes);
         fill_descs(bl, jobs, lease.ptr + desc_bytes + 256, host);
-        e = hipMemcpyAsync(desc_dev, host, ndesc * sizeof(JobDev), hipMemcpyHostToDevice, stream);
+        e = hipMemcpyAsync(desc_dev, host, staged, hipMemcpyHostToDevice, stream);
         pinned_give(c, pin, stream);
         if (e == hipSuccess) e = enqueue_batch(c, bl, desc_dev, counter, stream, false);
         pool_release(c, lease, stream);

@@ -40,12 +40,11 @@
 //   small      whole extraction of one job in one workgroup (L <= 2^14)
 #include <algorithm>
 #include <cstring>
-#include <tuple>
 #include <type_traits>
-#include <utility>
 
 #include "field.h"
 #include "kernels.h"
+#include "launch.h"
 
 // The file is compiled once per part (NTT_PART = 0..9) so that the template
 // instantiations build in parallel; without NTT_PART everything is built.
@@ -55,39 +54,6 @@
 #define NTT_HAS(k) (NTT_PART < 0 || NTT_PART == (k))
 
 namespace ext {
-
-// ------------------------------------------------------------------ launching
-
-extern thread_local GraphRecorder *t_graph_recorder;
-
-// Launches kern on stream s, or adds it to the recording graph of this thread.
-// The arguments are converted to the kernel's parameter types first; both paths
-// pass pointers to those values (a graph node copies them when it is added).
-template <typename... P, typename... A>
-static hipError_t launch_k(void (*kern)(P...), dim3 grid, dim3 block, size_t shmem, hipStream_t s, A &&...args) {
-    static_assert(sizeof...(P) == sizeof...(A), "argument count");
-    std::tuple<std::decay_t<P>...> vals(std::forward<A>(args)...);
-    void *ptrs[sizeof...(P) > 0 ? sizeof...(P) : 1];
-    std::apply([&](auto &...v) {
-        int i = 0;
-        ((ptrs[i++] = (void *)&v), ...);
-    }, vals);
-    if (GraphRecorder *r = t_graph_recorder) {
-        if (r->err != hipSuccess) return r->err;
-        hipKernelNodeParams kp = {};
-        kp.func = (void *)kern;
-        kp.gridDim = grid;
-        kp.blockDim = block;
-        kp.sharedMemBytes = (unsigned)shmem;
-        kp.kernelParams = ptrs;
-        kp.extra = nullptr;
-        hipGraphNode_t node = nullptr;
-        r->err = hipGraphAddKernelNode(&node, r->graph, r->last ? &r->last : nullptr, r->last ? 1 : 0, &kp);
-        if (r->err == hipSuccess) r->last = node;
-        return r->err;
-    }
-    return hipLaunchKernel((const void *)kern, grid, block, ptrs, shmem, s);
-}
 
 // ------------------------------------------------------------------ helpers
 
