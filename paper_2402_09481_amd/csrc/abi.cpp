@@ -703,6 +703,7 @@ namespace {
 
 // Rows, groups and workspace of a shape on the GF(2)[t] path (gf2.h: Gf2Job).
 struct Gf2Plan {
+    bool bits = false;  // the bit-by-bit kernel: no rows, no workspace
     uint32_t px = 0, ps = 0, pz = 0, splits = 1;
     uint32_t rows_lg = 0, hx = 0, hz = 0, nx = 0, nz = 0;
     size_t x = 0, s = 0, g = 0, xb = 0, sb = 0, flags = 0, total = 0;
@@ -712,10 +713,26 @@ struct Gf2Plan {
 // about as much as GF2_DIRECT_MAX of them at these sizes.
 constexpr uint64_t GF2_DIRECT_MAX = 12288;
 
+// Whether the bit-by-bit kernel takes a shape. It costs n m / 32 times three instructions.
+// A call of its own has the whole GPU for them: 6 us up to n = 2^14, 13 us at n = 2^16, m =
+// n / 2 (n m = 2^31), 25 us at 2^32 and 34 us at 2^33, where the transforms take 17 to 26 us
+// below 2^16 and 27 to 29 us at 2^17 and 2^18 (MI355X, back to back). A batch member
+// competes with the single-workgroup transform, which takes more at every size.
+constexpr uint64_t GF2_BITS_ONE = uint64_t(1) << 32;
+bool gf2_bits(const Shape &s, size_t jobs) {
+    const uint64_t n = conv_n(s);
+    if (n > uint64_t(32) * gf2::BITS_MAX_WORDS) return false;
+    return s.Lmin <= (uint64_t(1) << max_small_lg()) || (jobs == 1 && n * s.m <= GF2_BITS_ONE);
+}
+
 // jobs: how many extractions share the launch.
 Gf2Plan gf2_plan(const Shape &s, size_t jobs = 1) {
     const uint64_t B = gf2::BLOCK_BITS;
     Gf2Plan p;
+    if (gf2_bits(s, jobs)) {
+        p.bits = true;
+        return p;
+    }
     p.px = (uint32_t)((conv_n(s) + B - 1) / B);
     p.pz = (uint32_t)((s.m + B - 1) / B);
     p.ps = p.px + p.pz - 1;
@@ -770,15 +787,16 @@ constexpr uint64_t GF2_SINGLE_MIN = uint64_t(1) << 20;
 // seed spectrum, or has set the plan of this size class on this context.
 bool gf2_route(ext_ctx *c, const Shape &s, uint32_t flags, bool single) {
     if (!c->gf2 || (flags & (EXT_SINGLE_TRANSFORM | EXT_SEED_CACHED))) return false;
-    if (s.Lmin <= (single ? GF2_SINGLE_MIN : uint64_t(1) << max_small_lg())) return false;
+    if (single && s.Lmin <= GF2_SINGLE_MIN && !gf2_bits(s, 1)) return false;
     Plan p;
     if (make_plan(s.Lmin, 0, p) == EXT_OK) {
         std::lock_guard<std::mutex> g(c->mu);
         auto it = c->chosen.find(p.field * 64 + p.lg);
         if (it != c->chosen.end() && (it->second & (single ? 3 : 1))) return false;
     }
+    if (gf2_bits(s, single ? 1 : 2)) return true;
     if (plan_shape(c, s, p, flags, !single) != EXT_OK) return false;
-    return s.n <= (uint64_t(1) << 36) && gf2_plan(s).total <= workspace_layout(p).total;
+    return s.n <= (uint64_t(1) << 36) && gf2_plan(s, 2).total <= workspace_layout(p).total;
 }
 
 Gf2Job gf2_job(const Shape &s, const Gf2Plan &p, const uint64_t *x, const uint64_t *y, uint64_t *z, int32_t *status,
@@ -1073,6 +1091,11 @@ hipError_t enqueue(ext_ctx *c, const Plan &p, uint32_t njobs, const JobDev *jobs
 hipError_t enqueue_gf2(ext_ctx *c, const Gf2Job &j, hipStream_t s, bool quiet) {
     Tracer tr(c, s, quiet);
     tr.begin();
+    if (!j.px) {
+        const hipError_t e = launch_gf2_bits(gf2_bits_workgroups(j, false), nullptr, j, nullptr, s);
+        if (tr.on) tr.end("gf2_bits");
+        return e;
+    }
     hipError_t e = launch_gf2_fwd(gf2_fwd_workgroups(j), nullptr, j, nullptr, s);
     if (tr.on) tr.end("gf2_fwd");
     if (e != hipSuccess) return e;
@@ -1860,7 +1883,7 @@ struct BatchLayout {
     };
     struct Gf2Chunk {
         size_t first, n;
-        Gf2Launch fwd, mul, inv, rows_fwd[gf2::ROWS_LG_MAX + 1], rows_inv[gf2::ROWS_LG_MAX + 1];
+        Gf2Launch bits, fwd, mul, inv, rows_fwd[gf2::ROWS_LG_MAX + 1], rows_inv[gf2::ROWS_LG_MAX + 1];
     };
     std::vector<Gf2Chunk> gf2_chunks;
     size_t ntab = 0;
@@ -1886,6 +1909,10 @@ void layout_gf2(const std::vector<Member> &members, size_t cap, BatchLayout &bl)
             const Member &mb = *bl.gf2[i];
             ws += align256(mb.gp.total);
             const Gf2Job j = gf2_job(mb.shape, mb.gp, nullptr, nullptr, nullptr, nullptr, 0, nullptr);
+            if (mb.gp.bits) {
+                add(ch.bits, gf2_bits_workgroups(j, true));
+                continue;
+            }
             add(ch.fwd, gf2_fwd_workgroups(j));
             if (j.rows_lg) {
                 add(ch.rows_fwd[j.rows_lg], gf2_rows_fwd_workgroups(j));
@@ -1898,12 +1925,13 @@ void layout_gf2(const std::vector<Member> &members, size_t cap, BatchLayout &bl)
         ch.n = i - ch.first;
         bl.max_ws = std::max(bl.max_ws, ws);
         char b[96];
-        snprintf(b, sizeof b, "g%zu:%u:%u:%u", ch.n, ch.fwd.wgs, ch.mul.wgs, ch.inv.wgs);
+        snprintf(b, sizeof b, "g%zu:%u:%u:%u:%u", ch.n, ch.bits.wgs, ch.fwd.wgs, ch.mul.wgs, ch.inv.wgs);
         bl.sig += b;
         auto place = [&](BatchLayout::Gf2Launch &l) {
             l.tab = bl.ntab;
             bl.ntab += l.wgs;
         };
+        place(ch.bits);
         place(ch.fwd);
         place(ch.mul);
         place(ch.inv);
@@ -1989,7 +2017,7 @@ void fill_descs(const BatchLayout &bl, const ext_job *jobs, char *ws, char *stag
     Gf2Job *const gout = (Gf2Job *)(staged + bl.gf2_offset());
     uint2 *const tab = (uint2 *)(staged + bl.tab_offset());
     for (auto &ch : bl.gf2_chunks) {
-        size_t off = 0, fwd = ch.fwd.tab, mul = ch.mul.tab, inv = ch.inv.tab;
+        size_t off = 0, bits = ch.bits.tab, fwd = ch.fwd.tab, mul = ch.mul.tab, inv = ch.inv.tab;
         size_t rf[gf2::ROWS_LG_MAX + 1], ri[gf2::ROWS_LG_MAX + 1];
         for (int p = 0; p <= gf2::ROWS_LG_MAX; ++p) {
             rf[p] = ch.rows_fwd[p].tab;
@@ -2005,6 +2033,10 @@ void fill_descs(const BatchLayout &bl, const ext_job *jobs, char *ws, char *stag
             auto put = [&](size_t &at, uint32_t wgs) {
                 for (uint32_t w = 0; w < wgs; ++w) tab[at++] = make_uint2(k, w);
             };
+            if (mb.gp.bits) {
+                put(bits, gf2_bits_workgroups(d, true));
+                continue;
+            }
             put(fwd, gf2_fwd_workgroups(d));
             if (d.rows_lg) {
                 put(rf[d.rows_lg], gf2_rows_fwd_workgroups(d));
@@ -2045,6 +2077,7 @@ hipError_t enqueue_batch(ext_ctx *c, const BatchLayout &bl, char *staged_dev, ui
             e = launch(l.wgs, jobs, none, tab + l.tab);
             if (tr.on) tr.end(label);
         };
+        step("gf2_bits", ch.bits, [&](auto... a) { return launch_gf2_bits(a..., s); });
         step("gf2_fwd", ch.fwd, [&](auto... a) { return launch_gf2_fwd(a..., s); });
         step("gf2_mul", ch.mul, [&](auto... a) { return launch_gf2_mul(a..., s); });
         for (int p = gf2::ROWS_LG_MAX; p >= gf2::ROWS_LG_MIN; --p) {
@@ -2167,7 +2200,7 @@ extern "C" int extract_batch(ext_ctx *c, ext_job *jobs, size_t count, uint32_t f
         if (rc == EXT_OK && (j.flags & ~(EXT_SEED_LINEAR | EXT_SYNC | EXT_SINGLE_TRANSFORM))) rc = EXT_EINVAL;
         if (rc == EXT_OK && j.kind != EXT_KIND_TOEPLITZ && (j.flags & EXT_SEED_LINEAR)) rc = EXT_EINVAL;
         if (rc == EXT_OK) rc = validate(mb.shape, j.x, j.y, j.z, j.flags & EXT_SEED_LINEAR);
-        if (rc == EXT_OK && (mb.gf2 = gf2_route(c, mb.shape, j.flags, false))) mb.gp = gf2_plan(mb.shape, count);
+        if (rc == EXT_OK && (mb.gf2 = gf2_route(c, mb.shape, j.flags, false))) mb.gp = gf2_plan(mb.shape, std::max<size_t>(count, 2));
         else if (rc == EXT_OK) rc = plan_shape(c, mb.shape, mb.plan, j.flags, true);  // piece schedules included
         j.err = rc;
         if (rc != EXT_OK) {

@@ -69,6 +69,9 @@ constexpr uint32_t BLOCK_BITS = 1u << (ROW_LG - 1);
 constexpr uint32_t ROW_WORDS = 1u << (ROW_LG - 5);
 constexpr uint32_t SLICES = 64;
 
+// Input words of the longest extraction that the bit-by-bit kernel takes.
+constexpr int BITS_MAX_WORDS = 4096;
+
 // Rows of a transform over rows: 2^ROWS_LG_MIN .. 2^ROWS_LG_MAX.
 constexpr int ROWS_LG_MIN = 8, ROWS_LG_MAX = 12;
 
@@ -103,11 +106,13 @@ struct Gf2Job {
 // Workgroups of a job in each launch, and the launches: jobs and tab are device
 // arrays (tab: for every workgroup its job and its number within the job), or both
 // nullptr to run `one`.
+uint32_t gf2_bits_workgroups(const Gf2Job &j, bool many);  // the whole extraction bit by bit (many: in a batch)
 uint32_t gf2_fwd_workgroups(const Gf2Job &j);
 uint32_t gf2_mul_workgroups(const Gf2Job &j);       // direct
 uint32_t gf2_rows_fwd_workgroups(const Gf2Job &j);  // rows_lg > 0: transforms of X and S over rows,
 uint32_t gf2_rows_inv_workgroups(const Gf2Job &j);  // products and transforms back
 uint32_t gf2_inv_workgroups(const Gf2Job &j);
+hipError_t launch_gf2_bits(uint32_t wgs, const Gf2Job *jobs, const Gf2Job &one, const uint2 *tab, hipStream_t s);
 hipError_t launch_gf2_fwd(uint32_t wgs, const Gf2Job *jobs, const Gf2Job &one, const uint2 *tab, hipStream_t s);
 hipError_t launch_gf2_mul(uint32_t wgs, const Gf2Job *jobs, const Gf2Job &one, const uint2 *tab, hipStream_t s);
 // (every job of a launch has the given rows_lg)

@@ -1626,7 +1626,89 @@ __global__ void __launch_bounds__(64 * FWD_WAVES) __attribute__((amdgpu_waves_pe
     }
 }
 
+// ------------------------------------------------------------------ short extractions, bit by bit
+//
+// Up to BITS_MAX_WORDS input words the defining sum itself is the fastest way to a result: for
+// every input bit one funnel shift gives the 32 seed bits that meet a word of 32
+// outputs, and one AND-XOR adds them: 3 instructions (with the bit's mask) for 32
+// products, no passes and no workspace. A workgroup takes OW output words and the
+// whole input; a lane takes one output word and a share of the input words (the seed
+// window of the next input word is the last one's, moved by a word).
+constexpr int BITS_NT = 512;
+
+template <int OW>
+__global__ void __launch_bounds__(BITS_NT) k_gf2_bits(const Gf2Job *jobs, Gf2Job one, const uint2 *tab) {
+    constexpr int SUB = 64 / OW, SHARES = BITS_NT / 64 * SUB;
+    __shared__ u32 xw[BITS_MAX_WORDS], sw[BITS_MAX_WORDS + OW + 1];
+    __shared__ u32 part[BITS_NT / 64][OW];
+    __shared__ u32 seen[2];
+    const uint2 tw = tab ? tab[blockIdx.x] : make_uint2(0, blockIdx.x);
+    const Gf2Job &J = jobs ? jobs[tw.x] : one;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int n = (int)J.n, V = (n + 31) >> 5, w0 = (int)tw.y * OW;
+    // input words, and seed word t: positions 32 (w0 - V + 1 + t) + n - 32 ..
+    u32 one_ = 0, zero_ = 0;
+    if (tid < 2) seen[tid] = 0;
+    for (int v = tid; v < V; v += BITS_NT) {
+        const u32 x = input_word(J.ex, (int64_t)v * 32);
+        const u32 valid = n - v * 32 >= 32 ? ~0u : (1u << (n - v * 32)) - 1u;
+        one_ |= x;
+        zero_ |= ~x & valid;
+        xw[v] = x;
+    }
+    for (int t = tid; t < V + OW; t += BITS_NT) sw[t] = seed_word(J.ey, (int64_t)(w0 - V + 1 + t) * 32 + n - 32);
+    __syncthreads();
+    if (J.degen_n) {  // (the input words hold exactly the Dodis input's bits)
+        if (one_) atomicOr(&seen[0], 1u);
+        if (zero_) atomicOr(&seen[1], 1u);
+    }
+    const int w = lane % OW, share = wave * SUB + lane / OW, chunk = (V + SHARES - 1) / SHARES;
+    const int v0 = share * chunk, v1 = v0 + chunk < V ? v0 + chunk : V;
+    u32 acc0 = 0, acc1 = 0;
+    if (v0 < v1) {
+        u32 hi = sw[w + V - v0];
+        for (int v = v0; v < v1; ++v) {
+            const u32 lo = sw[w + V - 1 - v], x = xw[v];
+            unroll<0, 16>([&](auto b) {
+                acc0 = __builtin_amdgcn_bitop3_b32(acc0, __builtin_amdgcn_alignbit(hi, lo, 31 - 2 * b),
+                                                   bit_mask<2 * b>(x), 0x78);
+                acc1 = __builtin_amdgcn_bitop3_b32(acc1, __builtin_amdgcn_alignbit(hi, lo, 30 - 2 * b),
+                                                   bit_mask<2 * b + 1>(x), 0x78);
+            });
+            hi = lo;
+        }
+    }
+    u32 acc = acc0 ^ acc1;
+#pragma unroll
+    for (int o = OW; o < 64; o <<= 1) acc ^= bperm((lane ^ o) << 2, acc);
+    if (lane < OW) part[wave][lane] = acc;
+    __syncthreads();
+    const bool degen = J.degen_n && (seen[0] == 0 || seen[1] == 0);
+    if (tid < OW) {
+        u32 z = 0;
+#pragma unroll
+        for (int k = 0; k < BITS_NT / 64; ++k) z ^= part[k][tid];
+        const int zw = w0 + tid, m = (int)J.m, left = m - zw * 32;
+        if (degen || left <= 0) z = 0;
+        else if (left < 32) z &= (1u << left) - 1u;
+        if (zw < ((m + 63) >> 6) << 1) ((u32 *)J.z)[zw] = z;
+    }
+    if (tw.y == 0 && tid == 0 && J.status) *J.status = degen ? -3 : 0;
+}
+
 }  // namespace
+
+// (few workgroups of many lanes' work for a launch of its own; wider ones, which read the
+// input less often, where many jobs share it)
+constexpr int BITS_OW_ONE = 4, BITS_OW_MANY = 16;
+uint32_t gf2_bits_workgroups(const Gf2Job &j, bool many) {
+    const uint32_t ow = many ? BITS_OW_MANY : BITS_OW_ONE, words = (uint32_t)((j.m + 63) >> 6) << 1;
+    return (words + ow - 1) / ow;
+}
+hipError_t launch_gf2_bits(uint32_t wgs, const Gf2Job *jobs, const Gf2Job &one, const uint2 *tab, hipStream_t s) {
+    if (jobs) return launch_k(k_gf2_bits<BITS_OW_MANY>, dim3(wgs), dim3(BITS_NT), 0, s, jobs, one, tab);
+    return launch_k(k_gf2_bits<BITS_OW_ONE>, dim3(wgs), dim3(BITS_NT), 0, s, jobs, one, tab);
+}
 
 uint32_t gf2_fwd_workgroups(const Gf2Job &j) {
     const uint32_t rows = ((j.px + 1) & ~1u) + j.ps;

@@ -33,6 +33,40 @@ GF2_FN u32 bit_reverse(u32 v) {
 
 enum Side { T_FWD = 0, T_SEED = 1, T_OUT = 2 };
 
+// bits pos .. pos + 31 (any sign) of a string of len >= 1 bits, zero outside it
+GF2_FN u32 clip_word(const uint64_t *bits, uint64_t len, int64_t pos) {
+    if (pos >= (int64_t)len || pos <= -32) return 0u;
+    const u32 *b = (const u32 *)bits;
+    const int64_t w = pos >> 5, last = (int64_t)((len + 31) >> 5) - 1;
+    const u32 lo = w >= 0 ? load_word(b + w) : 0u, hi = w < last ? load_word(b + w + 1) : 0u;
+    const u32 v = funnel(hi, lo, (int)(pos & 31));
+    const int64_t left = (int64_t)len - pos;
+    return left < 32 ? v & ((1u << left) - 1u) : v;
+}
+
+// positions i .. i + 31 (i >= 0) of the input x' (PREFIX or REV), zero outside it
+GF2_FN u32 input_word(const Emb &e, int64_t i) {
+    if (e.mode == EMB_PREFIX) return clip_word(e.bits, e.len, i);
+    const u32 v = bit_reverse(clip_word(e.bits, e.len, (int64_t)e.N - 32 - i));
+    const int64_t left = (int64_t)e.a - i;
+    return left >= 32 ? v : left <= 0 ? 0u : v & ((1u << left) - 1u);
+}
+
+// seed positions k .. k + 31 (s_k = bit (k + rot) mod P for 0 <= k < N, zero outside); P may
+// be as small as 1
+GF2_FN u32 seed_word(const Emb &e, int64_t k) {
+    const int64_t N = (int64_t)e.N, P = (int64_t)e.P;
+    if (k >= N || k <= -32) return 0u;
+    int64_t r = k + (int64_t)e.rot;
+    while (r < 0) r += P;
+    while (r >= P) r -= P;
+    u32 v = 0u;
+    for (int64_t at = r; at > r - 32 - P && at > -32; at -= P) v |= clip_word(e.bits, e.P, at);
+    if (k < 0) v &= ~0u << (int)(-k);
+    if (N - k < 32) v &= (1u << (N - k)) - 1u;
+    return v;
+}
+
 // The 16 words from bit pos (any sign) of a string of len >= 1 bits, ORed into v; bits
 // outside the string are zero and no word outside it is read.
 GF2_FN void clip_run(u32 *v, const uint64_t *bits, uint64_t len, int64_t pos) {

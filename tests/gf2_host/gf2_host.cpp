@@ -25,17 +25,18 @@ void gf2_forms(uint32_t c, uint32_t *w) {
     const gf2::Forms f = gf2::forms81(c);
     for (int i = 0; i < 3; ++i) w[i] = f.w[i];
 }
-// 16 words of the input (seed = 0) or the seed from position pos; returns the reads outside
-// the string's dwords
-int gf2_run(int seed, int mode, const uint64_t *bits, uint64_t len, uint64_t a, uint64_t N, uint64_t rot, uint64_t P,
+// 16 words of the input (seed = 0) or the seed from position pos, read as one run or word
+// by word; returns the reads outside the string's dwords
+int gf2_run(int single, int seed, int mode, const uint64_t *bits, uint64_t len, uint64_t a, uint64_t N, uint64_t rot, uint64_t P,
             int64_t pos, uint32_t *out) {
     const Emb e{bits, len, a, N, rot, P, (uint32_t)mode, 0};
     g_lo = (const uint32_t *)bits;
     g_hi = g_lo + ((seed ? P : len) + 31) / 32;
     g_bad = 0;
     for (int k = 0; k < 16; ++k) out[k] = 0;
-    if (seed) gf2::seed_run(out, e, pos);
-    else gf2::input_run(out, e, pos);
+    for (int k = 0; single && k < 16; ++k) out[k] = seed ? gf2::seed_word(e, pos + 32 * k) : gf2::input_word(e, pos + 32 * k);
+    if (!single && seed) gf2::seed_run(out, e, pos);
+    if (!single && !seed) gf2::input_run(out, e, pos);
     return g_bad;
 }
 }

@@ -23,7 +23,7 @@ def lib(tmp_path_factory):
                            os.path.join(HERE, "gf2_host", "gf2_host.cpp")])
     L = ctypes.CDLL(out)
     u64 = ctypes.c_uint64
-    L.gf2_run.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_void_p, u64, u64, u64, u64, u64, ctypes.c_int64,
+    L.gf2_run.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_void_p, u64, u64, u64, u64, u64, ctypes.c_int64,
                           ctypes.c_void_p]
     for f in (L.gf2_mul, L.gf2_subspace):
         f.restype = ctypes.c_uint32
@@ -84,11 +84,14 @@ def _words(bits):
     return np.packbits(pad, bitorder="little").view(np.uint64).copy()
 
 
+@pytest.mark.parametrize("single", [0, 1])
 @pytest.mark.parametrize("form", ["prefix", "reversed", "reversed-short", "seed-linear", "seed-paper", "seed-periodic"])
-def test_runs_of_the_packed_strings(lib, form):
+def test_runs_of_the_packed_strings(lib, form, single):
     g = np.random.default_rng(len(form))
-    for n in [520, 1000, 4097, 16385]:
-        for m in sorted({1, 33, n // 2, n}):
+    for n in [520, 1000, 4097, 16385] + [1, 2, 5, 31, 33, 70] * single:
+        if n == 1 and form == "reversed-short":
+            continue
+        for m in sorted({1, min(33, n), n // 2 or 1, n}):
             N = n + m - 1
             if form.startswith("seed"):
                 P = N if form != "seed-periodic" else n
@@ -118,7 +121,7 @@ def test_runs_of_the_packed_strings(lib, form):
             for pos in edges:
                 if not seed:
                     pos = max(0, pos) & ~31  # input runs start at multiples of the run
-                bad = lib.gf2_run(seed, mode, w.ctypes.data, ln, a, NN, rot, P, pos, out.ctypes.data)
+                bad = lib.gf2_run(single, seed, mode, w.ctypes.data, ln, a, NN, rot, P, pos, out.ctypes.data)
                 got = np.unpackbits(out.view(np.uint8), bitorder="little")
                 want = np.array([full[k] if 0 <= k < len(full) else 0 for k in range(pos, pos + 512)], np.uint8)
                 assert bad == 0, (form, n, m, pos)

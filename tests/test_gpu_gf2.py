@@ -66,6 +66,30 @@ def _check(ctx, kind, n, m, order, rows):
     assert rc == 0 and np.array_equal(z, ref), (kind, n, m, order)
 
 
+@pytest.mark.parametrize("batch", [False, True])
+def test_bit_by_bit(ctx, batch):
+    """Short extractions: word and workgroup edges (4 and 16 output words), the longest input
+    and the most work that the kernel takes alone, and the longest in a batch."""
+    shapes = [(n, m) for n in (1, 2, 31, 32, 33, 63, 64, 65, 127, 129, 2048, 4096, 8191, 8192)
+              for m in sorted({1, n // 2 or 1, n})]
+    shapes += [(16383, 2)] + ([] if batch else [(131072, 32768), (65537, 65535), (16420, 9000), (131071, 1)])
+    for n, m in shapes:
+        kinds = [("toeplitz", "paper"), ("toeplitz", "linear")]
+        kinds += [("dodis", "paper")] if n > 3 and oracle.is_na_prime(n) else []
+        kinds += [("circulant", "paper")] if oracle.is_na_prime(n + 1) else []
+        for kind, order in kinds:
+            x, y = _inputs(kind, n, m, n + m)
+            show_case("gf2 bits", kind, n, m, order, batch)
+            if batch:
+                z, labels = _labels(ctx, lambda: _batch_of_one(ctx, kind, x, y, n, m, order))
+            else:
+                (code, z), labels = _labels(ctx, lambda: gpu_extract(ctx, kind, x, y, n, m, order))
+                assert code == 0
+            assert labels == ["gf2_bits"], labels
+            rc, ref = oracle.extract_product(kind, x, y, n, m, order)
+            assert rc == 0 and np.array_equal(z, ref), (kind, n, m, order)
+
+
 @pytest.mark.parametrize("order", ["paper", "linear"])
 @pytest.mark.parametrize("n,m", [(B, 2), (B, B), (B + 1, B), (2 * B - 1, B + 1), (2 * B, 1), (2 * B, 2 * B), (5 * B + 31, 3 * B - 33),
                                  (17 * B + 1, 16 * B), (300007, 100003), (128 * B, 96 * B)])
@@ -99,7 +123,7 @@ def test_periodic_seeds(ctx, kind, n, m):
 
 
 def test_degenerate_inputs(ctx):
-    for n in (65587, 1048589):
+    for n in (5, 4099, 65587, 1048589):
         y = W.bernoulli_bits(W.rng(3), n, 0.5)
         for x in (np.zeros(W.nwords(n), np.uint64), W.mask_tail(np.full(W.nwords(n), ~np.uint64(0)), n)):
             code, z = gpu_extract(ctx, "dodis", x, y, n, n // 2)
