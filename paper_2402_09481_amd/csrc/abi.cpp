@@ -706,12 +706,14 @@ struct Gf2Plan {
     bool bits = false;  // the bit-by-bit kernel: no rows, no workspace
     uint32_t px = 0, ps = 0, pz = 0, splits = 1;
     uint32_t rows_lg = 0, hx = 0, hz = 0, nx = 0, nz = 0;
-    size_t x = 0, s = 0, g = 0, xb = 0, sb = 0, flags = 0, total = 0;
+    size_t x = 0, s = 0, g = 0, xb = 0, sb = 0, pb = 0, flags = 0, total = 0;
 };
 
-// Product rows computed term by term cost px pz row products; a transform over rows costs
-// about as much as GF2_DIRECT_MAX of them at these sizes.
-constexpr uint64_t GF2_DIRECT_MAX = 12288;
+// Most row products px pz that are computed term by term rather than by a transform over
+// rows: alone, 12288 (the transform's two launches take 46 us from 2^8 rows on; 8385
+// products 13 us, 32768 34 us); where many jobs share the launches, 4096 (2^8 rows cost
+// about as much VALU work as that many products).
+constexpr uint64_t GF2_DIRECT_ONE = 12288, GF2_DIRECT_MANY = 4096;
 
 // Whether the bit-by-bit kernel takes a shape. It costs n m / 32 times three instructions.
 // A call of its own has the whole GPU for them: 6 us up to n = 2^14, 13 us at n = 2^16, m =
@@ -738,7 +740,7 @@ Gf2Plan gf2_plan(const Shape &s, size_t jobs = 1) {
     p.ps = p.px + p.pz - 1;
     const size_t row = gf2::ROW_WORDS * 4;
     size_t groups = 0;
-    if ((uint64_t)p.px * p.pz <= GF2_DIRECT_MAX) {
+    if ((uint64_t)p.px * p.pz <= (jobs > 1 ? GF2_DIRECT_MANY : GF2_DIRECT_ONE)) {
         // product rows: eight waves each, split further while fewer than 1024 waves run, and
         // so that no wave sums more than 32 products where others would wait for it
         const uint32_t fill = (uint32_t)(128 / std::min<size_t>(jobs, 128)), most = (p.px + 7) / 8;
@@ -770,7 +772,8 @@ Gf2Plan gf2_plan(const Shape &s, size_t jobs = 1) {
     p.g = p.s + p.ps * row;
     p.xb = p.g + (size_t)p.splits * p.pz * row;
     p.sb = p.xb + p.nx * groups;
-    p.flags = p.sb + (groups ? p.nx + p.nz - 1 : 0) * groups;
+    p.pb = p.sb + (groups ? p.nx + p.nz - 1 : 0) * groups;
+    p.flags = p.pb + (p.nx > 1 ? p.nz * groups : 0);
     p.total = p.flags + 256;
     return p;
 }
@@ -796,7 +799,7 @@ bool gf2_route(ext_ctx *c, const Shape &s, uint32_t flags, bool single) {
     }
     if (gf2_bits(s, single ? 1 : 2)) return true;
     if (plan_shape(c, s, p, flags, !single) != EXT_OK) return false;
-    return s.n <= (uint64_t(1) << 36) && gf2_plan(s, 2).total <= workspace_layout(p).total;
+    return s.n <= (uint64_t(1) << 36) && gf2_plan(s, single ? 1 : 2).total <= workspace_layout(p).total;
 }
 
 Gf2Job gf2_job(const Shape &s, const Gf2Plan &p, const uint64_t *x, const uint64_t *y, uint64_t *z, int32_t *status,
@@ -817,6 +820,7 @@ Gf2Job gf2_job(const Shape &s, const Gf2Plan &p, const uint64_t *x, const uint64
     j.G = (uint32_t *)(ws + p.g);
     j.XB = (uint32_t *)(ws + p.xb);
     j.SB = (uint32_t *)(ws + p.sb);
+    j.PB = (uint32_t *)(ws + p.pb);
     j.flags = (uint32_t *)(ws + p.flags);
     j.z = z;
     j.status = status;
@@ -1104,6 +1108,12 @@ hipError_t enqueue_gf2(ext_ctx *c, const Gf2Job &j, hipStream_t s, bool quiet) {
         e = launch_gf2_rows_fwd((int)j.rows_lg, gf2_rows_fwd_workgroups(j), nullptr, j, nullptr, s);
         if (tr.on) tr.end("gf2_rows_fwd");
         if (e != hipSuccess) return e;
+        if (j.nx > 1) {
+            tr.begin();
+            e = launch_gf2_rows_prod(j.nz == 1, gf2_rows_prod_workgroups(j), nullptr, j, nullptr, s);
+            if (tr.on) tr.end("gf2_rows_prod");
+            if (e != hipSuccess) return e;
+        }
         tr.begin();
         e = launch_gf2_rows_inv((int)j.rows_lg, gf2_rows_inv_workgroups(j), nullptr, j, nullptr, s);
         if (tr.on) tr.end("gf2_rows_inv");
@@ -1883,7 +1893,7 @@ struct BatchLayout {
     };
     struct Gf2Chunk {
         size_t first, n;
-        Gf2Launch bits, fwd, mul, inv, rows_fwd[gf2::ROWS_LG_MAX + 1], rows_inv[gf2::ROWS_LG_MAX + 1];
+        Gf2Launch bits, fwd, mul, inv, prod[2], rows_fwd[gf2::ROWS_LG_MAX + 1], rows_inv[gf2::ROWS_LG_MAX + 1];
     };
     std::vector<Gf2Chunk> gf2_chunks;
     size_t ntab = 0;
@@ -1916,6 +1926,7 @@ void layout_gf2(const std::vector<Member> &members, size_t cap, BatchLayout &bl)
             add(ch.fwd, gf2_fwd_workgroups(j));
             if (j.rows_lg) {
                 add(ch.rows_fwd[j.rows_lg], gf2_rows_fwd_workgroups(j));
+                add(ch.prod[j.nz == 1], gf2_rows_prod_workgroups(j));
                 add(ch.rows_inv[j.rows_lg], gf2_rows_inv_workgroups(j));
             } else {
                 add(ch.mul, gf2_mul_workgroups(j));
@@ -1935,6 +1946,11 @@ void layout_gf2(const std::vector<Member> &members, size_t cap, BatchLayout &bl)
         place(ch.fwd);
         place(ch.mul);
         place(ch.inv);
+        for (auto &l : ch.prod) {
+            place(l);
+            snprintf(b, sizeof b, ":%u", l.wgs);
+            bl.sig += b;
+        }
         for (int p = gf2::ROWS_LG_MIN; p <= gf2::ROWS_LG_MAX; ++p) {
             place(ch.rows_fwd[p]);
             place(ch.rows_inv[p]);
@@ -2018,7 +2034,7 @@ void fill_descs(const BatchLayout &bl, const ext_job *jobs, char *ws, char *stag
     uint2 *const tab = (uint2 *)(staged + bl.tab_offset());
     for (auto &ch : bl.gf2_chunks) {
         size_t off = 0, bits = ch.bits.tab, fwd = ch.fwd.tab, mul = ch.mul.tab, inv = ch.inv.tab;
-        size_t rf[gf2::ROWS_LG_MAX + 1], ri[gf2::ROWS_LG_MAX + 1];
+        size_t prod[2] = {ch.prod[0].tab, ch.prod[1].tab}, rf[gf2::ROWS_LG_MAX + 1], ri[gf2::ROWS_LG_MAX + 1];
         for (int p = 0; p <= gf2::ROWS_LG_MAX; ++p) {
             rf[p] = ch.rows_fwd[p].tab;
             ri[p] = ch.rows_inv[p].tab;
@@ -2040,6 +2056,7 @@ void fill_descs(const BatchLayout &bl, const ext_job *jobs, char *ws, char *stag
             put(fwd, gf2_fwd_workgroups(d));
             if (d.rows_lg) {
                 put(rf[d.rows_lg], gf2_rows_fwd_workgroups(d));
+                put(prod[d.nz == 1], gf2_rows_prod_workgroups(d));
                 put(ri[d.rows_lg], gf2_rows_inv_workgroups(d));
             } else {
                 put(mul, gf2_mul_workgroups(d));
@@ -2080,10 +2097,12 @@ hipError_t enqueue_batch(ext_ctx *c, const BatchLayout &bl, char *staged_dev, ui
         step("gf2_bits", ch.bits, [&](auto... a) { return launch_gf2_bits(a..., s); });
         step("gf2_fwd", ch.fwd, [&](auto... a) { return launch_gf2_fwd(a..., s); });
         step("gf2_mul", ch.mul, [&](auto... a) { return launch_gf2_mul(a..., s); });
-        for (int p = gf2::ROWS_LG_MAX; p >= gf2::ROWS_LG_MIN; --p) {
+        for (int p = gf2::ROWS_LG_MAX; p >= gf2::ROWS_LG_MIN; --p)
             step("gf2_rows_fwd", ch.rows_fwd[p], [&](auto... a) { return launch_gf2_rows_fwd(p, a..., s); });
+        for (int k = 0; k < 2; ++k)
+            step("gf2_rows_prod", ch.prod[k], [&](auto... a) { return launch_gf2_rows_prod(k == 1, a..., s); });
+        for (int p = gf2::ROWS_LG_MAX; p >= gf2::ROWS_LG_MIN; --p)
             step("gf2_rows_inv", ch.rows_inv[p], [&](auto... a) { return launch_gf2_rows_inv(p, a..., s); });
-        }
         step("gf2_inv", ch.inv, [&](auto... a) { return launch_gf2_inv(a..., s); });
         if (e != hipSuccess) return e;
     }

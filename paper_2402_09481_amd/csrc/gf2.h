@@ -84,13 +84,14 @@ constexpr int ROWS_LG_MIN = 8, ROWS_LG_MAX = 12;
 // G_r = sum_q X_q S_(r-q+px-1).
 //   direct (rows_lg = 0): the sums term by term.
 //   by a transform over 2^rows_lg rows: x' in nx groups of hx rows, z in nz groups of
-//   hz rows (hx + hz <= 2^rows_lg, and hx = hz unless nz = 1); XB and SB hold the
-//   transformed groups and the transformed nx + nz - 1 windows of hx + hz - 1 rows.
+//   hz rows (hx + hz - 1 <= 2^rows_lg, and hx = hz unless nz = 1); XB and SB hold the
+//   transformed groups and the transformed nx + nz - 1 windows of hx + hz - 1 rows, PB
+//   (nx > 1) the nz groups' sums of products.
 // Word (row r, slice s, plane e) of X and S is at r * rs + s * ss + e.
 struct Gf2Job {
     Emb ex, ey;
     uint32_t *X, *S, *G;
-    uint32_t *XB, *SB;
+    uint32_t *XB, *SB, *PB;
     uint64_t *z;
     int32_t *status;
     uint32_t *flags;      // degenerate check (JobDev::flags)
@@ -110,7 +111,8 @@ uint32_t gf2_bits_workgroups(const Gf2Job &j, bool many);  // the whole extracti
 uint32_t gf2_fwd_workgroups(const Gf2Job &j);
 uint32_t gf2_mul_workgroups(const Gf2Job &j);       // direct
 uint32_t gf2_rows_fwd_workgroups(const Gf2Job &j);  // rows_lg > 0: transforms of X and S over rows,
-uint32_t gf2_rows_inv_workgroups(const Gf2Job &j);  // products and transforms back
+uint32_t gf2_rows_prod_workgroups(const Gf2Job &j);  // sums of products (none when nx = 1)
+uint32_t gf2_rows_inv_workgroups(const Gf2Job &j);   // transforms back (nx = 1: products first)
 uint32_t gf2_inv_workgroups(const Gf2Job &j);
 hipError_t launch_gf2_bits(uint32_t wgs, const Gf2Job *jobs, const Gf2Job &one, const uint2 *tab, hipStream_t s);
 hipError_t launch_gf2_fwd(uint32_t wgs, const Gf2Job *jobs, const Gf2Job &one, const uint2 *tab, hipStream_t s);
@@ -118,6 +120,8 @@ hipError_t launch_gf2_mul(uint32_t wgs, const Gf2Job *jobs, const Gf2Job &one, c
 // (every job of a launch has the given rows_lg)
 hipError_t launch_gf2_rows_fwd(int rows_lg, uint32_t wgs, const Gf2Job *jobs, const Gf2Job &one, const uint2 *tab,
                                hipStream_t s);
+hipError_t launch_gf2_rows_prod(bool one_group, uint32_t wgs, const Gf2Job *jobs, const Gf2Job &one, const uint2 *tab,
+                                hipStream_t s);  // one_group: every job's nz is 1, or none's
 hipError_t launch_gf2_rows_inv(int rows_lg, uint32_t wgs, const Gf2Job *jobs, const Gf2Job &one, const uint2 *tab,
                                hipStream_t s);
 hipError_t launch_gf2_inv(uint32_t wgs, const Gf2Job *jobs, const Gf2Job &one, const uint2 *tab, hipStream_t s);

@@ -170,11 +170,14 @@ __device__ __forceinline__ void mul16(u32 *c, const u32 *a, const Fm &f) {
         c[i] ^= p[i];
         c[8 + i] ^= p[i];
     }
+    step_end();
     u32 s[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) s[i] = a[i] ^ a[8 + i];
     mul8<1>(c + 8, s, f);
+    step_end();
     mul8<2>(c, a + 8, f);
+    step_end();
 }
 
 // ------------------------------------------------------------------ moving index bits
@@ -1056,31 +1059,26 @@ __global__ void __launch_bounds__(64 * FWD_WAVES) __attribute__((amdgpu_waves_pe
 // The planes of a variable factor, its forms made as they are needed.
 struct PlaneForms {
     static constexpr bool CONSTANT = false;
-    u32 b[3][8];  // lo, lo + hi, x0x1x2 hi
-    __device__ __forceinline__ explicit PlaneForms(const u32 *y) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            b[0][i] = y[i];
-            b[1][i] = y[i] ^ y[8 + i];
-        }
-        u32 z[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        unroll<0, 8>([&](auto j) {
-            unroll<0, 8>([&](auto k) {
-                constexpr u32 p = fmul(1u << k, 0x80, 3);
-                if constexpr ((p >> j) & 1) z[j] ^= y[8 + k];
-            });
+    const u32 *y;
+    template <int H, int I>
+    __device__ __forceinline__ u32 plane() const {  // bit I of lo, lo + hi or x0x1x2 hi
+        if constexpr (H == 0) return y[I];
+        if constexpr (H == 1) return y[I] ^ y[8 + I];
+        u32 z = 0;
+        unroll<0, 8>([&](auto k) {
+            constexpr u32 p = fmul(1u << k, 0x80, 3);
+            if constexpr ((p >> I) & 1) z ^= y[8 + k];
         });
-#pragma unroll
-        for (int i = 0; i < 8; ++i) b[2][i] = z[i];
+        return z;
     }
     template <int H, int L, int I>
-    __device__ __forceinline__ u32 part() const {  // bit I of lo, lo + hi or x0x1 hi
-        if constexpr (L == 0) return b[H][I];
-        if constexpr (L == 1) return b[H][I] ^ b[H][4 + I];
+    __device__ __forceinline__ u32 part() const {  // bit I of that half's lo, lo + hi or x0x1 hi
+        if constexpr (L == 0) return plane<H, I>();
+        if constexpr (L == 1) return plane<H, I>() ^ plane<H, 4 + I>();
         u32 z = 0;
         unroll<0, 4>([&](auto k) {
             constexpr u32 p = fmul(1u << k, 8, 2);
-            if constexpr ((p >> I) & 1) z ^= b[H][4 + k];
+            if constexpr ((p >> I) & 1) z ^= plane<H, 4 + k>();
         });
         return z;
     }
@@ -1124,7 +1122,7 @@ __global__ void __launch_bounds__(64 * MUL_WAVES) k_gf2_mul(const Gf2Job *jobs, 
         u32 x[16], y[16];
         load_slice(x, J.X + (uint64_t)q * ROW_WORDS + lane * 16);
         load_slice(y, J.S + (uint64_t)(r + px - 1 - q) * ROW_WORDS + lane * 16);
-        mul16(acc, x, PlaneForms(y));
+        mul16(acc, x, PlaneForms{y});
     }
 #pragma unroll
     for (int g = 0; g < 4; ++g)
@@ -1157,7 +1155,8 @@ __global__ void __launch_bounds__(64 * MUL_WAVES) k_gf2_mul(const Gf2Job *jobs, 
 template <int P>
 struct Rows {
     static constexpr int ROWS = 1 << P, NT = ROWS / 4, WAVES = NT / 64;
-    static constexpr int LDS_WORDS = ROWS * 4 + ROWS / 4;  // four planes; a pad of four words per 16 rows
+    // eight planes, in two arrays of four; a pad of four words per 16 rows
+    static constexpr int PITCH = 16 * 4 + 4, HALF = ROWS / 16 * PITCH, LDS_WORDS = 2 * HALF;
     __device__ static __forceinline__ int at(int row) { return row * 4 + (row >> 4) * 4; }
 };
 
@@ -1196,6 +1195,79 @@ __device__ __forceinline__ void row_butterfly(u32 *f0, u32 *f1, const Fm &f) {
         mul_sub<BITS>(f1, f0, f);
     }
 }
+// Two products by one constant, leaf by leaf, so that they share its masks (nine at a
+// time: the masks of a whole product kept for the other would spill).
+template <int H, class Fm>
+__device__ __forceinline__ void mul8_two(u32 *c, const u32 *a, u32 *d, const u32 *b, const Fm &f) {
+    u32 p[4] = {0, 0, 0, 0}, q[4] = {0, 0, 0, 0};
+    mul4<H, 0>(p, a, f);
+    mul4<H, 0>(q, b, f);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        c[i] ^= p[i];
+        c[4 + i] ^= p[i];
+        d[i] ^= q[i];
+        d[4 + i] ^= q[i];
+    }
+    step_end();
+    const u32 s[4] = {a[0] ^ a[4], a[1] ^ a[5], a[2] ^ a[6], a[3] ^ a[7]};
+    const u32 t[4] = {b[0] ^ b[4], b[1] ^ b[5], b[2] ^ b[6], b[3] ^ b[7]};
+    mul4<H, 1>(c + 4, s, f);
+    mul4<H, 1>(d + 4, t, f);
+    step_end();
+    mul4<H, 2>(c, a + 4, f);
+    mul4<H, 2>(d, b + 4, f);
+    step_end();
+}
+template <int BITS, class Fm>
+__device__ __forceinline__ void mul_sub_two(u32 *c, const u32 *a, u32 *d, const u32 *b, const Fm &f) {
+    if constexpr (BITS == 4) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            mul4<0, 0>(c + 4 * g, a + 4 * g, f);
+            mul4<0, 0>(d + 4 * g, b + 4 * g, f);
+        }
+    } else if constexpr (BITS == 8) {
+        mul8_two<0>(c, a, d, b, f);
+        mul8_two<0>(c + 8, a + 8, d + 8, b + 8, f);
+    } else {
+        u32 p[8] = {0, 0, 0, 0, 0, 0, 0, 0}, q[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+        mul8_two<0>(p, a, q, b, f);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            c[i] ^= p[i];
+            c[8 + i] ^= p[i];
+            d[i] ^= q[i];
+            d[8 + i] ^= q[i];
+        }
+        step_end();
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            p[i] = a[i] ^ a[8 + i];
+            q[i] = b[i] ^ b[8 + i];
+        }
+        mul8_two<1>(c + 8, p, d + 8, q, f);
+        mul8_two<2>(c, a + 8, d, b + 8, f);
+    }
+}
+template <int BITS, bool INV, class Fm>
+__device__ __forceinline__ void row_butterfly_two(u32 *f0, u32 *f1, u32 *g0, u32 *g1, const Fm &f) {
+    if constexpr (!INV) {
+        mul_sub_two<BITS>(f0, f1, g0, g1, f);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            f1[e] ^= f0[e];
+            g1[e] ^= g0[e];
+        }
+    } else {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            f0[e] ^= f1[e];
+            g0[e] ^= g1[e];
+        }
+        mul_sub_two<BITS>(f1, f0, g1, g0, f);
+    }
+}
 constexpr int stage_bits(int i) { return i >= 8 ? 4 : i >= 4 ? 8 : 16; }  // of 2^12 rows; fewer rows need no more
 
 // The stages of row bits HI = 2k + 1 and 2k, held in the register number (rows 0..3: bits
@@ -1223,8 +1295,7 @@ __device__ __forceinline__ void row_round(u32 *v, u32 wave_row, u32 lane_row, u3
     auto hi = [&] {
         if constexpr (DO_HI) {
             const Fm f = forms(std::integral_constant<int, HI>());
-            row_butterfly<stage_bits(HI), INV>(v, v + 32, f);
-            row_butterfly<stage_bits(HI), INV>(v + 16, v + 48, f);
+            row_butterfly_two<stage_bits(HI), INV>(v, v + 32, v + 16, v + 48, f);
             step_end();
         }
     };
@@ -1281,52 +1352,77 @@ __device__ __forceinline__ void swap_row_lane(u32 *v) {
     }
 }
 
-// The basis change of 2^P rows of four planes in LDS.
+// The basis change of 2^P rows of eight planes in LDS, two planes to a thread. (The thread's
+// number is hidden from the optimizer at every step: it would otherwise keep the
+// addresses of all steps, for all planes, in registers, and spill.)
 template <int SIDE, int P>
 __device__ __forceinline__ void rows_basis(u32 *lds) {
     using Rw = Rows<P>;
-    const int t = threadIdx.x, pl = t & 3, u = t >> 2;  // u < ROWS / 16
-    auto units = [&](auto rr, int base, int stride) {
-        constexpr int R = decltype(rr)::value;
-        u32 a[1 << R];
-#pragma unroll
-        for (int k = 0; k < (1 << R); ++k) a[k] = lds[Rw::at(base + k * stride) + pl];
-        basis_units<SIDE, R>(a);
-#pragma unroll
-        for (int k = 0; k < (1 << R); ++k) lds[Rw::at(base + k * stride) + pl] = a[k];
+    auto thread = [](int &pl, int &u) {  // plane, and u < ROWS / 16
+        int t = threadIdx.x;
+        asm volatile("" : "+v"(t));
+        pl = t & 3;
+        u = t >> 2;
     };
+    // 2^R rows from word `at` on, `pitch` words apart
+    auto units = [&](auto rr, u32 *at, auto pitch) {
+        constexpr int R = decltype(rr)::value, D = decltype(pitch)::value;
+        u32 a[1 << R], c[1 << R];
+#pragma unroll
+        for (int k = 0; k < (1 << R); ++k) a[k] = at[k * D];
+#pragma unroll
+        for (int k = 0; k < (1 << R); ++k) c[k] = at[k * D + Rw::HALF];
+        basis_units<SIDE, R>(a);
+        basis_units<SIDE, R>(c);
+#pragma unroll
+        for (int k = 0; k < (1 << R); ++k) at[k * D] = a[k];
+#pragma unroll
+        for (int k = 0; k < (1 << R); ++k) at[k * D + Rw::HALF] = c[k];
+    };
+#define IC(x) std::integral_constant<int, x>()
     constexpr int R = P - 8;  // bits above the lower eight
-    auto top = [&] {          // those bits against the lower eight
+    auto classes = [&](auto kk, auto rr, int rho, u32 *base) {
+#pragma unroll 1
+        for (int h = 0; h < 2; ++h, base += Rw::HALF)
+            taylor_classes<SIDE, decltype(kk)::value, decltype(rr)::value>(
+                rho, [&](int row) { return base[Rw::at(row)]; }, [&](int row, u32 w) { base[Rw::at(row)] = w; });
+    };
+    auto top = [&] {  // those bits against the lower eight
         if constexpr (R > 0) {
             __syncthreads();
-            for (int rho = u; rho < 255; rho += Rw::ROWS / 16)
-                taylor_classes<SIDE, 8, R>(
-                    rho, [&](int row) { return lds[Rw::at(row) + pl]; }, [&](int row, u32 w) { lds[Rw::at(row) + pl] = w; });
+            int pl, u;
+            thread(pl, u);
+            for (int rho = u; rho < 255; rho += Rw::ROWS / 16) classes(IC(8), IC(R), rho, lds + pl);
         }
     };
     auto high = [&] {  // within them
         if constexpr (R > 1) {
             __syncthreads();
-            for (int base = u; base < 256; base += Rw::ROWS / 16) units(std::integral_constant<int, R>(), base, 256);
+            int pl, u;
+            thread(pl, u);
+            for (int base = u; base < 256; base += Rw::ROWS / 16)
+                units(IC(R), lds + Rw::at(base) + pl, IC(Rw::PITCH * 16));
         }
     };
     auto low_classes = [&] {  // bits 7..4 against 3..0
         __syncthreads();
-        if ((u & 15) < 15) {
-            const int g = (u >> 4) * 256;
-            taylor_classes<SIDE, 4, 4>(
-                u & 15, [&](int row) { return lds[Rw::at(g + row) + pl]; },
-                [&](int row, u32 w) { lds[Rw::at(g + row) + pl] = w; });
-        }
+        int pl, u;
+        thread(pl, u);
+        if ((u & 15) < 15) classes(IC(4), IC(4), u & 15, lds + (u >> 4) * 16 * Rw::PITCH + pl);
     };
     auto mid = [&] {
         __syncthreads();
-        units(std::integral_constant<int, 4>(), (u >> 4) * 256 + (u & 15), 16);
+        int pl, u;
+        thread(pl, u);
+        units(IC(4), lds + Rw::at((u >> 4) * 256 + (u & 15)) + pl, IC(Rw::PITCH));
     };
     auto low = [&] {
         __syncthreads();
-        units(std::integral_constant<int, 4>(), u * 16, 1);
+        int pl, u;
+        thread(pl, u);
+        units(IC(4), lds + u * Rw::PITCH + pl, IC(4));
     };
+#undef IC
     if constexpr (SIDE != T_OUT) {
         top();
         high();
@@ -1343,26 +1439,31 @@ __device__ __forceinline__ void rows_basis(u32 *lds) {
     __syncthreads();
 }
 
-// Moves v from rows row_out(b) to rows row_in(b) of this thread (b < 4), a quarter of the
-// planes at a time; step(lds) runs in between on the rows of four planes.
+// Moves v from rows row_out(b) to rows row_in(b) of this thread (b < 4), half of the planes at
+// a time; step(lds) runs in between on the rows of eight planes.
 template <int P, class Out, class In, class Step>
 __device__ __forceinline__ void rows_exchange(u32 *v, u32 *lds, Out &&row_out, In &&row_in, Step &&step) {
     using Rw = Rows<P>;
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
+    for (int c = 0; c < 2; ++c) {
 #pragma unroll
         for (int b = 0; b < 4; ++b)
-            *(uint4 *)(lds + Rw::at(row_out(b))) = make_uint4(v[b * 16 + 4 * c], v[b * 16 + 4 * c + 1],
-                                                              v[b * 16 + 4 * c + 2], v[b * 16 + 4 * c + 3]);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const u32 *q = v + b * 16 + 8 * c + 4 * h;
+                *(uint4 *)(lds + Rw::at(row_out(b)) + h * Rw::HALF) = make_uint4(q[0], q[1], q[2], q[3]);
+            }
         step(lds);
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            const uint4 q = *(const uint4 *)(lds + Rw::at(row_in(b)));
-            v[b * 16 + 4 * c] = q.x;
-            v[b * 16 + 4 * c + 1] = q.y;
-            v[b * 16 + 4 * c + 2] = q.z;
-            v[b * 16 + 4 * c + 3] = q.w;
-        }
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const uint4 q = *(const uint4 *)(lds + Rw::at(row_in(b)) + h * Rw::HALF);
+                v[b * 16 + 8 * c + 4 * h] = q.x;
+                v[b * 16 + 8 * c + 4 * h + 1] = q.y;
+                v[b * 16 + 8 * c + 4 * h + 2] = q.z;
+                v[b * 16 + 8 * c + 4 * h + 3] = q.w;
+            }
         __syncthreads();
     }
 }
@@ -1526,8 +1627,50 @@ k_gf2_rows_fwd(const Gf2Job *jobs, Gf2Job one, const uint2 *tab) {
     for (int k = 0; k < 64; k += 4) *(uint4 *)(out + k) = make_uint4(v[k], v[k + 1], v[k + 2], v[k + 3]);
 }
 
-// Backwards: workgroup = slice of a group of z: the sum of its products, the transform
-// back, and its rows (in reverse order) to G.
+// Sums of products of groups (more than one group of the input): a thread takes one row of
+// a slice in TG groups of z, whose seed windows it keeps in registers: the next input
+// group needs one new window, and the others shifted by one group.
+template <int TG>
+__global__ void __launch_bounds__(256) k_gf2_rows_prod(const Gf2Job *jobs, Gf2Job one, const uint2 *tab) {
+    const uint2 tw = tab ? tab[blockIdx.x] : make_uint2(0, blockIdx.x);
+    const Gf2Job &J = jobs ? jobs[tw.x] : one;
+    const u32 lg = J.rows_lg + 6, per = 1u << (lg - 8);  // rows of all slices of a group: 2^lg, `per` workgroups
+    const u32 g0 = tw.y / per * TG, nz = J.nz, nx = J.nx;
+    const uint64_t at = ((uint64_t)(tw.y % per) * 256 + threadIdx.x) * 16;
+    u32 acc[TG][16] = {}, s[TG][16];
+    // windows g0 + t + nx - 1 - q; before q = 0, those of t >= 1 in their places for t - 1
+#pragma unroll
+    for (int t = 1; t < TG; ++t) {
+        const u32 w = g0 + t + nx - 1;
+        load_slice(s[t - 1], J.SB + ((uint64_t)(w < nx + nz - 1 ? w : nx + nz - 2) << (lg + 4)) + at);
+    }
+    for (u32 q0 = 0; q0 < nx; q0 += TG) {
+#pragma unroll
+        for (int i = 0; i < TG; ++i) {  // (window of t at q0 + i: place (t - i - 1) mod TG)
+            const u32 q = q0 + i;
+            if (q >= nx) break;
+            u32 x[16];
+            load_slice(x, J.XB + ((uint64_t)q << (lg + 4)) + at);
+            load_slice(s[(2 * TG - i - 1) % TG], J.SB + ((uint64_t)(g0 + nx - 1 - q) << (lg + 4)) + at);
+#pragma unroll
+            for (int t = 0; t < TG; ++t) {
+                mul16(acc[t], s[(2 * TG + t - i - 1) % TG], PlaneForms{x});
+                step_end();
+            }
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < TG; ++t) {
+        if (g0 + t >= nz) break;
+        u32 *out = J.PB + ((uint64_t)(g0 + t) << (lg + 4)) + at;
+#pragma unroll
+        for (int k = 0; k < 16; k += 4) *(uint4 *)(out + k) = make_uint4(acc[t][k], acc[t][k + 1], acc[t][k + 2], acc[t][k + 3]);
+    }
+}
+
+// Backwards: workgroup = slice of a group of z: its product (or, with several groups of the
+// input, the sum that k_gf2_rows_prod left), the transform back, and its rows (in reverse
+// order) to G.
 template <int P>
 __global__ void __launch_bounds__(Rows<P>::NT) __attribute__((amdgpu_waves_per_eu(P == 12 ? 4 : 1)))
 k_gf2_rows_inv(const Gf2Job *jobs, Gf2Job one, const uint2 *tab) {
@@ -1536,16 +1679,20 @@ k_gf2_rows_inv(const Gf2Job *jobs, Gf2Job one, const uint2 *tab) {
     const uint2 tw = tab ? tab[blockIdx.x] : make_uint2(0, blockIdx.x);
     const Gf2Job &J = jobs ? jobs[tw.x] : one;
     const u32 sl = tw.y / J.nz, g = tw.y % J.nz;
-    u32 v[64] = {};
-    for (u32 q = 0; q < J.nx; ++q) {
-        const u32 *x = J.XB + ((uint64_t)(q * SLICES + sl) << (P + 4)) + threadIdx.x * 64;
-        const u32 *s = J.SB + ((uint64_t)((g + J.nx - 1 - q) * SLICES + sl) << (P + 4)) + threadIdx.x * 64;
+    u32 v[64];
+    const uint64_t at = ((uint64_t)(g * SLICES + sl) << (P + 4)) + threadIdx.x * 64;
+    if (J.nx > 1) {
+#pragma unroll
+        for (int b = 0; b < 4; ++b) load_slice(v + 16 * b, J.PB + at + 16 * b);
+    } else {  // (then nz is 1 as well)
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
             u32 a[16], c[16];
-            load_slice(a, x + 16 * b);
-            load_slice(c, s + 16 * b);
-            mul16(v + 16 * b, a, PlaneForms(c));
+            load_slice(a, J.XB + at + 16 * b);
+            load_slice(c, J.SB + at + 16 * b);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) v[16 * b + e] = 0u;
+            mul16(v + 16 * b, a, PlaneForms{c});
             step_end();
         }
     }
@@ -1716,6 +1863,16 @@ uint32_t gf2_fwd_workgroups(const Gf2Job &j) {
 }
 uint32_t gf2_mul_workgroups(const Gf2Job &j) { return j.pz * j.splits; }
 uint32_t gf2_rows_fwd_workgroups(const Gf2Job &j) { return (2 * j.nx + j.nz - 1) * SLICES; }
+// (four groups of z to a thread where there are that many)
+uint32_t gf2_rows_prod_workgroups(const Gf2Job &j) {
+    if (j.nx <= 1) return 0;
+    return (j.nz > 1 ? (j.nz + 3) / 4 : 1) * (SLICES << (j.rows_lg - 8));
+}
+hipError_t launch_gf2_rows_prod(bool one_group, uint32_t wgs, const Gf2Job *jobs, const Gf2Job &one, const uint2 *tab,
+                                hipStream_t s) {
+    if (one_group) return launch_k(k_gf2_rows_prod<1>, dim3(wgs), dim3(256), 0, s, jobs, one, tab);
+    return launch_k(k_gf2_rows_prod<4>, dim3(wgs), dim3(256), 0, s, jobs, one, tab);
+}
 uint32_t gf2_rows_inv_workgroups(const Gf2Job &j) { return j.nz * SLICES; }
 uint32_t gf2_inv_workgroups(const Gf2Job &j) { return (j.pz + 2 * FWD_WAVES - 1) / (2 * FWD_WAVES); }
 

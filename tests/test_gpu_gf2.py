@@ -60,8 +60,8 @@ def _check(ctx, kind, n, m, order, rows):
         assert code == 0
     else:  # (alone, these run the transform)
         z, labels = _labels(ctx, lambda: _batch_of_one(ctx, kind, x, y, n, m, order))
-    want = ["gf2_fwd", "gf2_rows_fwd", "gf2_rows_inv", "gf2_inv"] if rows else ["gf2_fwd", "gf2_mul", "gf2_inv"]
-    assert labels == want, labels
+    steps = ["gf2_rows_fwd", "gf2_rows_inv"] if rows else ["gf2_mul"]
+    assert [lab for lab in labels if lab != "gf2_rows_prod"] == ["gf2_fwd"] + steps + ["gf2_inv"], labels
     rc, ref = oracle.extract_product(kind, x, y, n, m, order)
     assert rc == 0 and np.array_equal(z, ref), (kind, n, m, order)
 
