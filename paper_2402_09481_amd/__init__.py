@@ -257,6 +257,17 @@ class Context:
         library's return code and the per-job host validation codes. graph=True records
         the launch sequence of this batch signature into a HIP graph and replays it."""
         arr = (ExtJob * len(jobs))()
+        marshal = _lib.marshal()
+        if not marshal.fill(jobs, ctypes.addressof(arr)):  # a job of another than the ordinary form
+            self._fill_jobs(jobs, arr)
+        fn = self._lib.extract_batch_unbatched if unbatched else self._lib.extract_batch
+        flags = (EXT_SYNC if sync else 0) | (_lib.EXT_GRAPH if (graph and not unbatched) else 0)
+        rc = fn(self.handle, arr, len(jobs), flags, _stream_handle(stream, self.device))
+        return rc, marshal.errs(ctypes.addressof(arr), len(jobs))
+
+    @staticmethod
+    def _fill_jobs(jobs, arr):
+        """The job array, every job checked and converted; raises on the first bad one."""
         for i, j in enumerate(jobs):
             kind = j["kind"]
             if kind not in ("toeplitz", "circulant", "dodis"):
@@ -276,10 +287,6 @@ class Context:
                 _check_len(j["z"], m, "job %d: z" % i)
             st = _status_ptr(j.get("status"))
             arr[i].status = st.value if st is not None else None
-        fn = self._lib.extract_batch_unbatched if unbatched else self._lib.extract_batch
-        flags = (EXT_SYNC if sync else 0) | (_lib.EXT_GRAPH if (graph and not unbatched) else 0)
-        rc = fn(self.handle, arr, len(jobs), flags, _stream_handle(stream, self.device))
-        return rc, [arr[i].err for i in range(len(jobs))]
 
 
 _default = {}

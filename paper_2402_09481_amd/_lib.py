@@ -136,6 +136,26 @@ def load() -> ctypes.CDLL:
     return lib
 
 
+_marshal = None
+
+
+def marshal():
+    """The host module that fills a batch's job array (csrc/marshal.cpp)."""
+    global _marshal
+    if _marshal is None:
+        import importlib.machinery
+        import importlib.util
+        path = os.path.join(HERE, "_marshal.so")
+        if not os.path.exists(path):
+            raise ImportError("_marshal.so is not built (%s). Build it with `python -m paper_2402_09481_amd.build`." % path)
+        import torch  # noqa: F401  (its libraries are the module's)
+        loader = importlib.machinery.ExtensionFileLoader("_marshal", path)
+        mod = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_marshal", path, loader=loader))
+        loader.exec_module(mod)
+        _marshal = mod
+    return _marshal
+
+
 def strerror(code: int) -> str:
     try:
         return load().ext_strerror(int(code)).decode()

@@ -1,4 +1,4 @@
-"""Build libextractor.so (gfx950) in-tree with hipcc.
+"""Build libextractor.so (gfx950) in-tree with hipcc, and the host module _marshal.so.
 
 The transform kernel file is compiled as several parts in parallel (one per
 group of template instantiations), the GF(2)[t] kernels, the Von Neumann kernels
@@ -10,10 +10,12 @@ import concurrent.futures as cf
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libextractor.so")
+MARSHAL = os.path.join(HERE, "_marshal.so")
 BUILD = os.path.join(HERE, "_build")
 ARCH = os.environ.get("EXT_OFFLOAD_ARCH", "gfx950")
 
@@ -39,9 +41,23 @@ def _run(cmd):
     return out
 
 
+def _marshal_job():
+    """The Python module that fills a batch's job array (host code only, against torch)."""
+    import torch
+    root = os.path.dirname(torch.__file__)
+    tmp = MARSHAL + ".tmp%d" % os.getpid()
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch.compiled_with_cxx11_abi(),
+           "-I" + sysconfig.get_paths()["include"], "-I" + os.path.join(root, "include"),
+           "-I" + os.path.join(root, "include", "torch", "csrc", "api", "include"),
+           os.path.join(CSRC, "marshal.cpp"), "-o", tmp, "-L" + os.path.join(root, "lib"), "-ltorch_python",
+           "-ltorch_cpu", "-lc10"]
+    return cmd, tmp
+
+
 def build(verbose: bool = False) -> str:
     os.makedirs(BUILD, exist_ok=True)
-    jobs = []
+    jobs = [_marshal_job()]
     for part in range(NTT_PARTS):
         obj = os.path.join(BUILD, "ntt_part%d.o" % part)
         jobs.append(([HIPCC] + FLAGS + ["-DNTT_PART=%d" % part, "-c", os.path.join(CSRC, "ntt.hip"), "-o", obj], obj))
@@ -53,8 +69,9 @@ def build(verbose: bool = False) -> str:
         for out in ex.map(lambda j: _run(j[0]), jobs):
             if verbose and out.strip():
                 print(out)
+    os.replace(jobs[0][1], MARSHAL)
     tmp = OUT + ".tmp%d" % os.getpid()
-    _run([HIPCC, "--offload-arch=" + ARCH, "-shared", "-o", tmp] + [j[1] for j in jobs])
+    _run([HIPCC, "--offload-arch=" + ARCH, "-shared", "-o", tmp] + [j[1] for j in jobs[1:]])
     os.replace(tmp, OUT)
     return OUT
 

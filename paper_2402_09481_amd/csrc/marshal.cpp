@@ -1,0 +1,133 @@
+// Python module _marshal: fills the ext_job array of a batch from a list of job dicts.
+// What the binding's Python loop does (Context.batch), for jobs of the ordinary form;
+// fill() returns False at the first job of any other form (other types, a tensor off the GPU,
+// too short or not contiguous, ...), and the Python loop then handles the whole batch and
+// raises what it has to. Measured on 4096 jobs: 9.7 ms in Python.
+#include <Python.h>
+
+#include <ATen/core/Tensor.h>
+#include <torch/csrc/autograd/python_variable.h>
+
+#include "../../include/extractor.h"
+
+namespace {
+
+PyObject *k_kind, *k_n, *k_m, *k_x, *k_y, *k_z, *k_order, *k_single, *k_status, *v_linear;
+PyObject *kinds[3];
+
+uint64_t words(uint64_t bits) { return (bits + 63) >> 6; }
+
+// an exact non-negative Python int below 2^62
+bool get_int(PyObject *o, uint64_t &v) {
+    if (!o || !PyLong_CheckExact(o)) return false;
+    int overflow = 0;
+    const long long x = PyLong_AsLongLongAndOverflow(o, &overflow);
+    if (overflow || x < 0 || x >= (1ll << 62)) return false;
+    v = (uint64_t)x;
+    return true;
+}
+
+// the tensor, if it holds at least `need` packed words on the GPU
+bool get_words(PyObject *o, uint64_t need, const uint64_t *&p) {
+    if (!o || !THPVariable_CheckExact(o)) return false;
+    const at::Tensor &t = THPVariable_Unpack(o);
+    if (!t.is_cuda() || !t.is_contiguous() || t.element_size() != 8 || (uint64_t)t.numel() < need) return false;
+    p = static_cast<const uint64_t *>(t.data_ptr());
+    return true;
+}
+
+bool fill_job(PyObject *job, ext_job &out) {
+    if (!PyDict_CheckExact(job)) return false;
+    PyObject *kind = PyDict_GetItemWithError(job, k_kind);
+    if (!kind || !PyUnicode_CheckExact(kind)) return false;
+    int k = 0;
+    while (k < 3 && kind != kinds[k] && PyUnicode_Compare(kind, kinds[k]) != 0) ++k;
+    if (k == 3) return false;
+    uint64_t n = 0, m = 0;
+    if (!get_int(PyDict_GetItemWithError(job, k_n), n) || !get_int(PyDict_GetItemWithError(job, k_m), m)) return false;
+    // the buffer lengths are checked for the sizes that the library accepts (it rejects the others)
+    const bool sized = m >= 1 && m <= n && n <= (uint64_t(1) << 40);
+    const uint64_t seed = k == EXT_KIND_TOEPLITZ ? n + m - 1 : k == EXT_KIND_CIRCULANT ? n + 1 : n;
+    const uint64_t *x, *y, *z;
+    if (!get_words(PyDict_GetItemWithError(job, k_x), sized ? words(n) : 0, x) ||
+        !get_words(PyDict_GetItemWithError(job, k_y), sized ? words(seed) : 0, y) ||
+        !get_words(PyDict_GetItemWithError(job, k_z), sized ? words(m) : 0, z))
+        return false;
+    uint32_t flags = 0;
+    if (PyObject *o = PyDict_GetItemWithError(job, k_order)) {
+        if (!PyUnicode_CheckExact(o)) return false;
+        if (PyUnicode_Compare(o, v_linear) == 0) flags |= EXT_SEED_LINEAR;
+    }
+    if (PyObject *o = PyDict_GetItemWithError(job, k_single)) {
+        if (o == Py_True) flags |= EXT_SINGLE_TRANSFORM;
+        else if (o != Py_False && o != Py_None) return false;
+    }
+    int32_t *status = nullptr;
+    if (PyObject *o = PyDict_GetItemWithError(job, k_status); o && o != Py_None) {
+        if (!THPVariable_CheckExact(o)) return false;
+        const at::Tensor &t = THPVariable_Unpack(o);
+        if (!t.is_cuda() || t.scalar_type() != at::kInt || t.numel() < 1) return false;
+        status = static_cast<int32_t *>(t.data_ptr());
+    }
+    out = ext_job{k, flags, n, m, x, y, const_cast<uint64_t *>(z), status, 0, 0};
+    return true;
+}
+
+// fill(jobs, address of the ext_job array of len(jobs) entries) -> bool
+PyObject *fill(PyObject *, PyObject *args) {
+    PyObject *jobs;
+    unsigned long long addr;
+    if (!PyArg_ParseTuple(args, "OK", &jobs, &addr)) return nullptr;
+    if (!PyList_CheckExact(jobs)) Py_RETURN_FALSE;
+    ext_job *out = reinterpret_cast<ext_job *>(addr);
+    try {
+        for (Py_ssize_t i = 0; i < PyList_GET_SIZE(jobs); ++i)
+            if (!fill_job(PyList_GET_ITEM(jobs, i), out[i])) {
+                PyErr_Clear();
+                Py_RETURN_FALSE;
+            }
+    } catch (...) {  // (a tensor without storage: the Python loop raises torch's error)
+        PyErr_Clear();
+        Py_RETURN_FALSE;
+    }
+    Py_RETURN_TRUE;
+}
+
+// errs(address, count) -> [err of every job]
+PyObject *errs(PyObject *, PyObject *args) {
+    unsigned long long addr;
+    Py_ssize_t n;
+    if (!PyArg_ParseTuple(args, "Kn", &addr, &n)) return nullptr;
+    const ext_job *jobs = reinterpret_cast<const ext_job *>(addr);
+    PyObject *list = PyList_New(n);
+    if (!list) return nullptr;
+    for (Py_ssize_t i = 0; i < n; ++i) {
+        PyObject *v = PyLong_FromLong(jobs[i].err);
+        if (!v) {
+            Py_DECREF(list);
+            return nullptr;
+        }
+        PyList_SET_ITEM(list, i, v);
+    }
+    return list;
+}
+
+PyMethodDef methods[] = {{"fill", fill, METH_VARARGS, "fill(jobs, address) -> bool"},
+                         {"errs", errs, METH_VARARGS, "errs(address, count) -> list"},
+                         {nullptr, nullptr, 0, nullptr}};
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit__marshal(void) {
+    struct {
+        PyObject **at;
+        const char *text;
+    } names[] = {{&k_kind, "kind"}, {&k_n, "n"}, {&k_m, "m"}, {&k_x, "x"}, {&k_y, "y"}, {&k_z, "z"},
+                 {&k_order, "seed_order"}, {&k_single, "single_transform"}, {&k_status, "status"}, {&v_linear, "linear"},
+                 {&kinds[EXT_KIND_TOEPLITZ], "toeplitz"}, {&kinds[EXT_KIND_CIRCULANT], "circulant"},
+                 {&kinds[EXT_KIND_DODIS], "dodis"}};
+    for (auto &e : names)
+        if (!(*e.at = PyUnicode_InternFromString(e.text))) return nullptr;
+    return PyModule_Create(&module);
+}
