@@ -18,7 +18,7 @@
 
 #include "field.h"
 #include "gf2.h"
-#include "kernels.h"
+#include "launch.h"
 
 using namespace ext;
 
@@ -845,6 +845,7 @@ Gf2Job gf2_job(const Shape &s, const Gf2Plan &p, const uint64_t *x, const uint64
 struct Lease {
     char *ptr = nullptr;
     size_t size = 0;
+    LaunchEvent done;  // for the release, where the last launch can carry it
 };
 
 // Take a block of at least `size` bytes usable on `stream`.
@@ -900,14 +901,36 @@ int pool_acquire(ext_ctx *c, size_t size, hipStream_t stream, Lease &out) {
     return EXT_OK;
 }
 
+// The block's event orders device work only (streams of this device, and the host's
+// hipEventQuery before a free), so it needs no system-scope fence.
+hipError_t release_event(hipEvent_t *ev) {
+    return hipEventCreateWithFlags(ev, hipEventDisableTiming | hipEventDisableSystemFence);
+}
+
+// Before a call's launches: gives the lease an event that its last launch will carry.
+// Not while the stream is captured: there the release records an event, as a capture
+// node of its own.
+LaunchEvent *lease_event(Lease &l, hipStream_t stream) {
+    if (!l.ptr) return nullptr;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    if (release_event(&l.done.ev) != hipSuccess) l.done.ev = nullptr;
+    return &l.done;
+}
+
 void pool_release(ext_ctx *c, Lease &l, hipStream_t stream) {
     if (!l.ptr) return;
+    set_launch_event(nullptr);
     Block b;
     b.ptr = l.ptr;
     b.size = l.size;
     b.stream = stream;
-    b.used = hipEventCreateWithFlags(&b.ev, hipEventDisableTiming) == hipSuccess;
-    if (b.used) hipEventRecord(b.ev, stream);
+    b.ev = l.done.ev;
+    b.used = b.ev || release_event(&b.ev) == hipSuccess;
+    if (b.used && !l.done.recorded) hipEventRecord(b.ev, stream);
     std::lock_guard<std::mutex> g(c->mu);
     c->leased -= l.size;
     c->free_blocks.push_back(b);
@@ -968,14 +991,15 @@ enum Phase { PH_COLD = 0, PH_SEED_ONLY = 1, PH_WARM = 2, PH_FWD_BOTH = 3, PH_TWO
 
 // The launches of one extraction phase for njobs jobs (descriptors jobs_dev, or
 // the single job `one`). quiet: no tracing events (graph recording and the
-// allocation-free entry point).
-
+// allocation-free entry point). done: goes with the last launch.
 hipError_t enqueue(ext_ctx *c, const Plan &p, uint32_t njobs, const JobDev *jobs_dev, const JobDev *one,
-                   uint64_t max_m, bool any_degen, hipStream_t s, bool quiet = false, Phase ph = PH_COLD) {
+                   uint64_t max_m, bool any_degen, hipStream_t s, bool quiet = false, Phase ph = PH_COLD,
+                   LaunchEvent *done = nullptr) {
     const Tables &tb = c->tb[p.field];
     Tracer tr(c, s, quiet);
     if (p.small) {
         tr.begin();
+        set_launch_event(done);
         hipError_t e = launch_small(p.lg, njobs, jobs_dev, one, tb, s);
         if (tr.on) tr.end(pass_label("small", p.field, p.lg, 0));
         return e;
@@ -1046,6 +1070,12 @@ hipError_t enqueue(ext_ctx *c, const Plan &p, uint32_t njobs, const JobDev *jobs
     // length out_len is m for every shape built here (batch descriptors included);
     // a single job's own out_len is honoured as well.
     const uint64_t max_out = one ? std::max<uint64_t>(max_m, one->out_len) : max_m;
+    // for the 32-bit fields the last inverse pass writes z; for the 64-bit field the
+    // parity transpose writes z itself (the degenerate check ran with the
+    // embedding), unless a job folds (z_i = c_i ^ c_(i+n), which reads the packed
+    // parity string): batch descriptors never fold
+    const bool fold = one && one->nfold;
+    const bool by_inverse = !fold && p.field != FIELD_GL;
     uint64_t out_rows = 0;
     uint64_t mp[4] = {0, 0, 0, 0};  // the block size M before level i (nlev <= 4)
     uint64_t M = L;
@@ -1071,28 +1101,26 @@ hipError_t enqueue(ext_ctx *c, const Plan &p, uint32_t njobs, const JobDev *jobs
         pl.jobs = jobs_dev;
         pl.one = one;
         tr.begin();
+        if (i == 0 && by_inverse) set_launch_event(done);
         e = launch_strided(pl, tb, s);
         if (tr.on) tr.end(pass_label("strided", p.field, pl.lgr, pl.mode, fused));
         if (e != hipSuccess) return e;
     }
-    // the 32-bit fields' last inverse pass has written z; for the 64-bit field the
-    // parity transpose writes z itself (the degenerate check ran with the
-    // embedding), unless a job folds (z_i = c_i ^ c_(i+n), which reads the packed
-    // parity string): batch descriptors never fold
-    const bool fold = one && one->nfold;
-    if (!fold && p.field != FIELD_GL) return hipSuccess;
+    if (by_inverse) return hipSuccess;
     tr.begin();
+    if (!fold) set_launch_event(done);
     e = launch_ptrans(p.field, uint64_t(1) << p.lgr[0], L >> p.lgr[0], out_rows, njobs, jobs_dev, one, !fold, s);
     if (tr.on) tr.end(fold ? "ptrans" : "ptrans_pack");
     if (e != hipSuccess || !fold) return e;
     tr.begin();
+    set_launch_event(done);
     e = launch_pack(njobs, words(max_m), jobs_dev, one, s);
     if (tr.on) tr.end("pack");
     return e;
 }
 
 // The launches of one extraction on the GF(2)[t] path.
-hipError_t enqueue_gf2(ext_ctx *c, const Gf2Job &j, hipStream_t s, bool quiet) {
+hipError_t enqueue_gf2(ext_ctx *c, const Gf2Job &j, hipStream_t s, bool quiet, LaunchEvent *done = nullptr) {
     Tracer tr(c, s, quiet);
     tr.begin();
     if (!j.px) {
@@ -1124,6 +1152,7 @@ hipError_t enqueue_gf2(ext_ctx *c, const Gf2Job &j, hipStream_t s, bool quiet) {
     }
     if (e != hipSuccess) return e;
     tr.begin();
+    set_launch_event(done);
     e = launch_gf2_inv(gf2_inv_workgroups(j), nullptr, j, nullptr, s);
     if (tr.on) tr.end("gf2_inv");
     return e;
@@ -1225,7 +1254,8 @@ ext_ctx::SeedEntry *seed_entry(ext_ctx *c, const Shape &sh, const Plan &p, const
 
 // The launches of one extraction by number-theoretic transform (workspace ws).
 hipError_t enqueue_transform(ext_ctx *c, const Shape &sh, const Plan &p, const uint64_t *x, const uint64_t *y,
-                             uint64_t *z, int32_t *st, uint32_t flags, char *ws, hipStream_t s) {
+                             uint64_t *z, int32_t *st, uint32_t flags, char *ws, hipStream_t s,
+                             LaunchEvent *done) {
     JobDev jd = make_jobdev(sh, p, x, y, z, st, flags, ws);
     hipError_t e = hipSuccess;
     // (the two-piece schedule does not use the seed cache)
@@ -1245,14 +1275,15 @@ hipError_t enqueue_transform(ext_ctx *c, const Shape &sh, const Plan &p, const u
         se->busy--;
         return e;
     }
-    if (p.pieces < 2) return enqueue(c, p, 1, nullptr, &jd, sh.m, jd.degen_n != 0, s);
+    if (p.pieces < 2) return enqueue(c, p, 1, nullptr, &jd, sh.m, jd.degen_n != 0, s, false, PH_COLD, done);
     // the last piece's product, then each earlier piece's product plus the sum
     // so far, then the first piece fused with that sum, one inverse, parity
     for (int q = p.pieces - 1; q >= 1 && e == hipSuccess; --q) {
         const JobDev jq = make_jobdev(sh, p, x, y, z, st, flags, ws, q);
         e = enqueue(c, p, 1, nullptr, &jq, sh.m, false, s, false, q == p.pieces - 1 ? PH_FWD_BOTH : PH_FWD_ACC);
     }
-    return e == hipSuccess ? enqueue(c, p, 1, nullptr, &jd, sh.m, jd.degen_n != 0, s, false, PH_TWO) : e;
+    return e == hipSuccess ? enqueue(c, p, 1, nullptr, &jd, sh.m, jd.degen_n != 0, s, false, PH_TWO, done)
+                           : e;
 }
 
 int extract_one(ext_ctx *c, int kind, const uint64_t *x, uint64_t n, const uint64_t *y, uint64_t m, uint64_t *z,
@@ -1281,8 +1312,9 @@ int extract_one(ext_ctx *c, int kind, const uint64_t *x, uint64_t n, const uint6
         *mine = 0;
         st = mine;
     }
-    const hipError_t e = gf2 ? enqueue_gf2(c, gf2_job(sh, gp, x, y, z, st, flags, lease.ptr), s, false)
-                             : enqueue_transform(c, sh, p, x, y, z, st, flags, lease.ptr, s);
+    LaunchEvent *done = lease_event(lease, s);
+    const hipError_t e = gf2 ? enqueue_gf2(c, gf2_job(sh, gp, x, y, z, st, flags, lease.ptr), s, false, done)
+                             : enqueue_transform(c, sh, p, x, y, z, st, flags, lease.ptr, s, done);
     pool_release(c, lease, s);
     if (e != hipSuccess) {
         if (mine) give_pinned_status(c, mine);
@@ -1764,6 +1796,7 @@ int extract_von_neumann(ext_ctx *c, const uint64_t *x, uint64_t n, uint64_t *z, 
     }
     if (e == hipSuccess) {
         tr.begin();
+        set_launch_event(lease_event(lease, s));
         e = launch_vn_fix(w, n, z, z_words, m_out, st, s);
         tr.end("vn_fix");
     }

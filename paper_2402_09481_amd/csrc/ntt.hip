@@ -1536,6 +1536,8 @@ hipError_t launch_contig_p0(const PassLaunch &p, const Tables &t, hipStream_t s)
 #if NTT_HAS(4)
 thread_local GraphRecorder *t_graph_recorder = nullptr;
 void set_graph_recorder(GraphRecorder *rec) { t_graph_recorder = rec; }
+thread_local LaunchEvent *t_launch_event = nullptr;
+void set_launch_event(LaunchEvent *le) { t_launch_event = le && le->ev ? le : nullptr; }
 
 // the 32-bit fields share tile sizes
 int max_strided_lg(int field) { return field == FIELD_GL ? GL_STRIDED_MAX : BB_STRIDED_MAX; }

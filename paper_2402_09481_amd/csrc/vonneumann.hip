@@ -32,7 +32,7 @@
 #include <stdint.h>
 
 #include "../../include/extractor.h"
-#include "kernels.h"
+#include "launch.h"
 
 namespace ext {
 namespace {
@@ -403,8 +403,7 @@ VnWork vn_work(char *ws, uint64_t n) {
 hipError_t launch_vn_zero(const VnWork &w, uint64_t n, hipStream_t s) {
     const uint64_t T = vn_tiles(n);
     const uint64_t items = T > 2 ? T : 2;
-    hipLaunchKernelGGL(k_vn_zero, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, s, w, T);
-    return hipGetLastError();
+    return launch_k(k_vn_zero, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, s, w, T);
 }
 
 hipError_t launch_vn_main(const uint64_t *x, uint64_t n, uint64_t *z, uint64_t zcap, const VnWork &w, hipStream_t s) {
@@ -412,15 +411,13 @@ hipError_t launch_vn_main(const uint64_t *x, uint64_t n, uint64_t *z, uint64_t z
     const uint64_t nb = n & ~1ull;  // bits that form pairs
     const uint64_t nwords = (nb + 63) >> 6;
     const uint64_t last_mask = (nb & 63) ? ((1ull << (nb & 63)) - 1) : ~0ull;
-    hipLaunchKernelGGL(k_vn_main, dim3((unsigned)T), dim3(VN_NT), 0, s, x, nwords, last_mask, z, zcap, w, (uint32_t)T);
-    return hipGetLastError();
+    return launch_k(k_vn_main, dim3((unsigned)T), dim3(VN_NT), 0, s, x, nwords, last_mask, z, zcap, w, (uint32_t)T);
 }
 
 hipError_t launch_vn_fix(const VnWork &w, uint64_t n, uint64_t *z, uint64_t zcap, uint64_t *m_out, int32_t *status,
                          hipStream_t s) {
     const uint64_t T = vn_tiles(n);
-    hipLaunchKernelGGL(k_vn_fix, dim3((unsigned)((T + 255) / 256)), dim3(256), 0, s, w, T, z, zcap, m_out, status);
-    return hipGetLastError();
+    return launch_k(k_vn_fix, dim3((unsigned)((T + 255) / 256)), dim3(256), 0, s, w, T, z, zcap, m_out, status);
 }
 
 }  // namespace ext
