@@ -1158,6 +1158,40 @@ hipError_t enqueue_gf2(ext_ctx *c, const Gf2Job &j, hipStream_t s, bool quiet, L
     return e;
 }
 
+// The launches of one Von Neumann extraction in the workspace `lease`.
+hipError_t enqueue_vn(ext_ctx *c, const uint64_t *x, uint64_t n, uint64_t *z, uint64_t z_words, uint64_t *m_out,
+                      int32_t *st, Lease &lease, hipStream_t s) {
+    Tracer tr(c, s, false);
+    LaunchEvent *done = lease_event(lease, s);
+    hipError_t e;
+    if (vn_two_pass(n)) {
+        const VnPairWork w = vn_pair_work(lease.ptr, n);
+        tr.begin();
+        e = launch_vn_count(x, n, w, s);
+        if (tr.on) tr.end("vn_count");
+        if (e != hipSuccess) return e;
+        tr.begin();
+        set_launch_event(done);
+        e = launch_vn_pack(x, n, z, z_words, w, m_out, st, s);
+        if (tr.on) tr.end("vn_pack");
+        return e;
+    }
+    const VnWork w = vn_work(lease.ptr, n);
+    tr.begin();
+    e = launch_vn_zero(w, n, s);
+    if (tr.on) tr.end("vn_zero");
+    if (e != hipSuccess) return e;
+    tr.begin();
+    e = launch_vn_main(x, n, z, z_words, w, s);
+    if (tr.on) tr.end("vn_main");
+    if (e != hipSuccess) return e;
+    tr.begin();
+    set_launch_event(done);
+    e = launch_vn_fix(w, n, z, z_words, m_out, st, s);
+    if (tr.on) tr.end("vn_fix");
+    return e;
+}
+
 int32_t *take_pinned_status(ext_ctx *c) {
     std::lock_guard<std::mutex> g(c->mu);
     if (!c->pinned_status.empty()) {
@@ -1784,22 +1818,7 @@ int extract_von_neumann(ext_ctx *c, const uint64_t *x, uint64_t n, uint64_t *z, 
         *mine = 0;
         st = mine;
     }
-    const VnWork w = vn_work(lease.ptr, n);
-    Tracer tr(c, s, false);
-    tr.begin();
-    hipError_t e = launch_vn_zero(w, n, s);
-    tr.end("vn_zero");
-    if (e == hipSuccess) {
-        tr.begin();
-        e = launch_vn_main(x, n, z, z_words, w, s);
-        tr.end("vn_main");
-    }
-    if (e == hipSuccess) {
-        tr.begin();
-        set_launch_event(lease_event(lease, s));
-        e = launch_vn_fix(w, n, z, z_words, m_out, st, s);
-        tr.end("vn_fix");
-    }
+    const hipError_t e = enqueue_vn(c, x, n, z, z_words, m_out, st, lease, s);
     pool_release(c, lease, s);
     if (e != hipSuccess) {
         if (mine) give_pinned_status(c, mine);

@@ -199,6 +199,16 @@ struct VnWork {
     uint64_t *pl;
     uint32_t *counter;
 };
+// Two passes: per tile its first 64 kept bits and its count of them.
+struct VnPairWork {
+    uint64_t *head;
+    uint32_t *count;
+};
+bool vn_two_pass(uint64_t n);
+VnPairWork vn_pair_work(char *ws, uint64_t n);
+hipError_t launch_vn_count(const uint64_t *x, uint64_t n, const VnPairWork &w, hipStream_t s);
+hipError_t launch_vn_pack(const uint64_t *x, uint64_t n, uint64_t *z, uint64_t zcap, const VnPairWork &w,
+                          uint64_t *m_out, int32_t *status, hipStream_t s);
 uint64_t vn_tiles(uint64_t n);
 size_t vn_workspace_bytes(uint64_t n);
 VnWork vn_work(char *ws, uint64_t n);

@@ -2,8 +2,13 @@
 // x_{2j} when x_{2j} != x_{2j+1} and nothing otherwise; Alg. 3 walks the pairs
 // in order and appends).
 //
-// The output is a stream compaction of the input's pairs, done in one pass
-// over the input:
+// The output is a stream compaction of the input's pairs. Up to VN_TWO_MAX input bits
+// it takes two passes over the input:
+//
+//   k_vn_count one workgroup per tile of VP_TILE_W words: its count of differing pairs.
+//   k_vn_pack  sums the counts before its tile, compresses the tile and writes it.
+//
+// and beyond, where the second reading would come from HBM, one pass:
 //
 //   k_vn_zero  clears the tile states and the tile ticket counter.
 //   k_vn_main  one workgroup per tile of VN_TILE_W input words, in the order
@@ -53,6 +58,11 @@ static_assert(VN_OBUF <= VN_RAW, "output buffer aliases the input tile");
 static_assert(VN_WPT >= 2 && VN_WPT <= 32, "words per thread");
 static_assert(VN_NT >= 256 && VN_NT <= 1024 && VN_NT % 64 == 0, "the byte table is filled by the first 256 threads");
 
+// Two passes up to here: the second pass reads the input from the 256 MB last-level
+// cache as long as it is kept there. One pass against two, us: n = 10^6 14.3 / 9.1,
+// 2^27 19.0 / 12.8, 5*10^8 40.9 / 30.3, 2^30 68.2 / 56.2, 3*2^29 87.7 / 80.0,
+// 2^31 121 / 121, 3*2^30 172 / 213.
+constexpr uint64_t VN_TWO_MAX = 3ull << 29;
 constexpr uint64_t ST_AGG = 1ull << 62, ST_PREFIX = 2ull << 62, ST_ERR = 3ull << 62;
 constexpr uint64_t ST_VAL = (1ull << 62) - 1;
 constexpr uint32_t VN_SPIN_LIMIT = 1u << 22;
@@ -378,16 +388,234 @@ __global__ void k_vn_fix(VnWork w, uint64_t T, uint64_t *__restrict__ z, uint64_
     if (ql < zcap) z[ql] = v;
 }
 
+// ---------------------------------------------------------------- two passes (up to VN_TWO_MAX bits)
+
+// k_vn_count leaves every tile's count of differing pairs and its first 64 kept bits.
+// k_vn_pack sums the counts before its tile itself: no ticket, no look-back, no tile
+// waits for another, and the tile's place in z is known before its bits are assembled,
+// so they go straight onto the output's word grid, two input words at a time. An output
+// word that tiles share is stored by the one it begins in, from the first bits of the
+// tiles after it. (Where tiles met in the workspace by atomics instead, with the counts
+// in the same lines, that took 17 us.) A thread's eight words are loaded from where they
+// are (64 bytes a lane: the second half of a line comes from the L1), not staged through
+// LDS. At n = 5*10^8 (62.5 MB in, half of the pairs kept) the call went from 43.6 to
+// 30.1 us: the count 11 us, the cache's 6 TB/s; the packing 19 us, of which 6.5 go to the
+// byte table's reads and shifts and the rest to loads and stores over two rounds of
+// workgroups that are not full. Tiles of 256 threads x 16 words or 1024 x 4: 3 and 5 us
+// more.
+constexpr int VP_NT = 512;
+constexpr int VP_WPT = 8;
+constexpr int VP_TILE_W = VP_NT * VP_WPT;
+constexpr int VP_OBUF = VP_TILE_W / 2 + 3;
+constexpr int VP_NW = VP_NT / 64;
+
+// Inclusive sums over a wave, in six dependent adds that read other lanes directly.
+__device__ __forceinline__ uint32_t wave_scan32(uint32_t v) {
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false);  // row_shr:1, 2, 4, 8
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);  // row_bcast:15 to rows 1, 3
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);  // row_bcast:31 to rows 2, 3
+    return v;
+}
+__device__ __forceinline__ uint32_t last_lane(uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)v, 63); }
+
+typedef uint64_t WordPair __attribute__((ext_vector_type(2), aligned(8)));
+
+// The eight consecutive words of thread tid in tile t; words past the pairs read as 0.
+__device__ __forceinline__ void load_eight(const uint64_t *__restrict__ x, uint64_t nwords, uint64_t last_mask,
+                                           uint32_t t, int tid, uint64_t (&v)[VP_WPT]) {
+    const uint64_t base = (uint64_t)t * VP_TILE_W + VP_WPT * tid;
+    if ((uint64_t)(t + 1) * VP_TILE_W < nwords) {
+#pragma unroll
+        for (int k = 0; k < VP_WPT; k += 2) {
+            const WordPair p = *(const WordPair *)(x + base + k);
+            v[k] = p.x;
+            v[k + 1] = p.y;
+        }
+        return;
+    }
+#pragma unroll
+    for (int k = 0; k < VP_WPT; ++k) {
+        v[k] = base + k < nwords ? x[base + k] : 0;
+        if (base + k == nwords - 1) v[k] &= last_mask;
+    }
+}
+
+__global__ __launch_bounds__(VP_NT) void k_vn_count(const uint64_t *__restrict__ x, uint64_t nwords,
+                                                    uint64_t last_mask, VnPairWork w) {
+    __shared__ uint32_t wsum[VP_NW];
+    __shared__ uint64_t head;
+    __shared__ uint8_t tab[256];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    uint64_t v[VP_WPT];
+    load_eight(x, nwords, last_mask, blockIdx.x, tid, v);
+    if (tid < 256) tab[tid] = (uint8_t)byte_entry((uint32_t)tid);
+    if (tid == 0) head = 0;
+    uint32_t mine = 0;
+#pragma unroll
+    for (int k = 0; k < VP_WPT; ++k) mine += pairs_differing(v[k]);
+    const uint32_t incl = wave_scan32(mine);
+    if (lane == 63) wsum[wave] = incl;
+    __syncthreads();
+    uint32_t sum = 0, pos = incl - mine;
+#pragma unroll
+    for (int k = 0; k < VP_NW; ++k) {
+        pos += k < wave ? wsum[k] : 0u;
+        sum += wsum[k];
+    }
+    if (mine && pos < 64) {
+#pragma unroll
+        for (int k = 0; k < VP_WPT; ++k) {
+            uint32_t c;
+            const uint32_t bits = vn_word(v[k], tab, c);
+            if (c && pos < 64) atomicOr((unsigned long long *)&head, (unsigned long long)bits << pos);
+            pos += c;
+        }
+    }
+    __syncthreads();
+    if (tid == 0) {
+        w.count[blockIdx.x] = sum;
+        w.head[blockIdx.x] = head;
+    }
+}
+
+__global__ __launch_bounds__(VP_NT) void k_vn_pack(const uint64_t *__restrict__ x, uint64_t nwords,
+                                                   uint64_t last_mask, uint64_t *__restrict__ z, uint64_t zcap,
+                                                   VnPairWork w, uint32_t T, uint64_t *m_out, int32_t *status) {
+    __shared__ uint64_t obuf[VP_OBUF];
+    __shared__ uint8_t tab[256];
+    __shared__ uint32_t wsum[VP_NW], wbefore[VP_NW], wtotal[VP_NW];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t t = blockIdx.x;
+    uint64_t v[VP_WPT];
+    load_eight(x, nwords, last_mask, t, tid, v);
+    uint32_t before = 0, total = 0;
+    for (uint32_t i0 = tid; i0 < T; i0 += 4 * VP_NT) {  // four loads in flight
+        uint32_t c[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) c[k] = i0 + k * VP_NT < T ? w.count[i0 + k * VP_NT] : 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            total += c[k];
+            before += i0 + k * VP_NT < t ? c[k] : 0;
+        }
+    }
+    // wave 1: the 64 tiles after this one
+    uint32_t u = t + 1 + lane, next = 0;
+    uint64_t head = 0;
+    if (wave == 1 && u < T) {
+        next = w.count[u];
+        head = w.head[u];
+    }
+    if (tid < 256) tab[tid] = (uint8_t)byte_entry((uint32_t)tid);
+    for (int i = tid; i < VP_OBUF; i += VP_NT) obuf[i] = 0;
+    __syncthreads();
+
+    uint64_t kept[VP_WPT / 2];  // the bits kept from two words each
+    uint32_t cnt[VP_WPT / 2], mine = 0;
+#pragma unroll
+    for (int i = 0; i < VP_WPT / 2; ++i) {
+        uint32_t c0, c1;
+        const uint32_t lo = vn_word(v[2 * i], tab, c0), hi = vn_word(v[2 * i + 1], tab, c1);
+        kept[i] = lo | (uint64_t)hi << c0;
+        cnt[i] = c0 + c1;
+        asm volatile("" : "+v"(kept[i]), "+v"(cnt[i]));  // packed here, not at the assembly
+        mine += cnt[i];
+    }
+    const uint32_t incl = wave_scan32(mine);
+    before = wave_scan32(before);
+    total = wave_scan32(total);
+    if (lane == 63) {
+        wsum[wave] = incl;
+        wbefore[wave] = before;
+        wtotal[wave] = total;
+    }
+    __syncthreads();
+    uint32_t agg = 0, pos = incl - mine;
+    before = total = 0;
+#pragma unroll
+    for (int k = 0; k < VP_NW; ++k) {
+        pos += k < wave ? wsum[k] : 0u;
+        agg += wsum[k];
+        before += wbefore[k];
+        total += wtotal[k];
+    }
+    if (t == 0 && tid == 0) {
+        *m_out = total;
+        if (status) *status = total ? EXT_OK : EXT_EDEGENERATE;
+    }
+    if (agg == 0) return;
+
+    const uint32_t sft = before & 63;  // the tile's first bit in its first output word
+    uint32_t p = sft + pos;
+#pragma unroll
+    for (int i = 0; i < VP_WPT / 2; ++i) {
+        const uint32_t wi = p >> 6, sh = p & 63;
+        // (nothing is ORed where nothing is kept: with few differing pairs all lanes
+        // would take turns at one word)
+        if (cnt[i]) atomicOr((unsigned long long *)&obuf[wi], (unsigned long long)(kept[i] << sh));
+        if (sh + cnt[i] > 64) atomicOr((unsigned long long *)&obuf[wi + 1], (unsigned long long)(kept[i] >> (64 - sh)));
+        p += cnt[i];
+    }
+    __syncthreads();
+    // this tile's words: from the first one that begins in it to the last
+    const uint64_t q0 = before >> 6;
+    const uint32_t end = sft + agg, nq = (end + 63) >> 6;
+    const bool tail = (end & 63) != 0;  // the last word is not full
+    for (uint32_t q = tid + (sft != 0); q < nq - tail; q += VP_NT)
+        if (q0 + q < zcap) z[q0 + q] = obuf[q];
+    if (wave == 1 && tail && (nq > 1 || sft == 0)) {
+        const uint64_t q = q0 + nq - 1;
+        const uint32_t left = total - (uint32_t)(q << 6) < 64 ? total - (uint32_t)(q << 6) : 64;  // bits of the word
+        uint32_t has = end & 63;
+        uint64_t part = 0;
+        while (has < left) {  // (at the last tile has = left: each turn looks at tiles that are there)
+            next = next < 64 ? next : 64;
+            const uint32_t sum = wave_scan32(next), at = has + sum - next;
+            if (at < 64) part |= head << at;
+            has += last_lane(sum);
+            if (has >= left) break;
+            u += 64;
+            next = u < T ? w.count[u] : 0;
+            head = u < T ? w.head[u] : 0;
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) part |= __shfl_xor(part, o);
+        if (lane == 0 && q < zcap) z[q] = obuf[nq - 1] | part;
+    }
+}
+
 }  // namespace
 
-uint64_t vn_tiles(uint64_t n) {
-    const uint64_t nwords = ((n & ~1ull) + 63) >> 6;
-    return nwords ? (nwords + VN_TILE_W - 1) / VN_TILE_W : 0;
+namespace {
+struct VnInput {
+    uint64_t nwords;     // words that hold pairs
+    uint64_t last_mask;  // the pairs' bits in the last of them
+};
+VnInput vn_input(uint64_t n) {
+    const uint64_t nb = n & ~1ull;
+    return VnInput{(nb + 63) >> 6, (nb & 63) ? ((1ull << (nb & 63)) - 1) : ~0ull};
 }
+uint64_t vn_pair_tiles(uint64_t n) { return (vn_input(n).nwords + VP_TILE_W - 1) / VP_TILE_W; }
+}  // namespace
+
+uint64_t vn_tiles(uint64_t n) { return (vn_input(n).nwords + VN_TILE_W - 1) / VN_TILE_W; }
 
 size_t vn_workspace_bytes(uint64_t n) {
     const uint64_t T = vn_tiles(n);
     return (size_t)(3 * T * 8 + 256);
+}
+
+// (12 bytes for each of the at most twice as many tiles: within vn_workspace_bytes)
+VnPairWork vn_pair_work(char *ws, uint64_t n) {
+    VnPairWork w;
+    w.head = (uint64_t *)ws;
+    w.count = (uint32_t *)(w.head + vn_pair_tiles(n));
+    return w;
 }
 
 VnWork vn_work(char *ws, uint64_t n) {
@@ -400,6 +628,21 @@ VnWork vn_work(char *ws, uint64_t n) {
     return w;
 }
 
+bool vn_two_pass(uint64_t n) { return n <= VN_TWO_MAX; }
+
+hipError_t launch_vn_count(const uint64_t *x, uint64_t n, const VnPairWork &w, hipStream_t s) {
+    const VnInput in = vn_input(n);
+    return launch_k(k_vn_count, dim3((unsigned)vn_pair_tiles(n)), dim3(VP_NT), 0, s, x, in.nwords, in.last_mask, w);
+}
+
+hipError_t launch_vn_pack(const uint64_t *x, uint64_t n, uint64_t *z, uint64_t zcap, const VnPairWork &w,
+                          uint64_t *m_out, int32_t *status, hipStream_t s) {
+    const VnInput in = vn_input(n);
+    const uint64_t T = vn_pair_tiles(n);
+    return launch_k(k_vn_pack, dim3((unsigned)T), dim3(VP_NT), 0, s, x, in.nwords, in.last_mask, z, zcap, w, (uint32_t)T,
+                    m_out, status);
+}
+
 hipError_t launch_vn_zero(const VnWork &w, uint64_t n, hipStream_t s) {
     const uint64_t T = vn_tiles(n);
     const uint64_t items = T > 2 ? T : 2;
@@ -408,10 +651,8 @@ hipError_t launch_vn_zero(const VnWork &w, uint64_t n, hipStream_t s) {
 
 hipError_t launch_vn_main(const uint64_t *x, uint64_t n, uint64_t *z, uint64_t zcap, const VnWork &w, hipStream_t s) {
     const uint64_t T = vn_tiles(n);
-    const uint64_t nb = n & ~1ull;  // bits that form pairs
-    const uint64_t nwords = (nb + 63) >> 6;
-    const uint64_t last_mask = (nb & 63) ? ((1ull << (nb & 63)) - 1) : ~0ull;
-    return launch_k(k_vn_main, dim3((unsigned)T), dim3(VN_NT), 0, s, x, nwords, last_mask, z, zcap, w, (uint32_t)T);
+    const VnInput in = vn_input(n);
+    return launch_k(k_vn_main, dim3((unsigned)T), dim3(VN_NT), 0, s, x, in.nwords, in.last_mask, z, zcap, w, (uint32_t)T);
 }
 
 hipError_t launch_vn_fix(const VnWork &w, uint64_t n, uint64_t *z, uint64_t zcap, uint64_t *m_out, int32_t *status,
