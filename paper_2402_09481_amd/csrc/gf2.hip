@@ -160,9 +160,9 @@ __device__ __forceinline__ void mul8(u32 *c, const u32 *a, const Fm &f) {
     mul4<H, 2>(c, a + 4, f);
 }
 
-// c += a * b over the field of 2^16
+// c += a * b over the field of 2^16, in three parts
 template <class Fm>
-__device__ __forceinline__ void mul16(u32 *c, const u32 *a, const Fm &f) {
+__device__ __forceinline__ void mul16_low(u32 *c, const u32 *a, const Fm &f) {
     u32 p[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     mul8<0>(p, a, f);
 #pragma unroll
@@ -170,11 +170,19 @@ __device__ __forceinline__ void mul16(u32 *c, const u32 *a, const Fm &f) {
         c[i] ^= p[i];
         c[8 + i] ^= p[i];
     }
-    step_end();
+}
+template <class Fm>
+__device__ __forceinline__ void mul16_sum(u32 *c, const u32 *a, const Fm &f) {
     u32 s[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) s[i] = a[i] ^ a[8 + i];
     mul8<1>(c + 8, s, f);
+}
+template <class Fm>
+__device__ __forceinline__ void mul16(u32 *c, const u32 *a, const Fm &f) {
+    mul16_low(c, a, f);
+    step_end();
+    mul16_sum(c, a, f);
     step_end();
     mul8<2>(c, a + 8, f);
     step_end();
@@ -1568,6 +1576,44 @@ __device__ __forceinline__ void rows_stages(u32 *v, u32 *lds, u32 plus_one) {
 #undef IC
 }
 
+// XB, SB and PB hold the 2^P rows of a slice as the threads of k_gf2_rows_fwd and _inv
+// have them: wave by wave, the b-th row of its 64 lanes (b < 4), four words of a lane
+// beside those of the next, so that every load and store of a wave is one piece of
+// 1 KB. (The products are row by row: any order serves.) Words of a row's 64 lanes:
+constexpr u32 UNIT = 64 * 16;
+__device__ __forceinline__ u32 unit_at(u32 thread) { return (thread >> 6) * 4 * UNIT + (thread & 63) * 4; }
+__device__ __forceinline__ void load_unit(u32 *x, const u32 *p) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const u32x4 q = *(const __attribute__((address_space(1))) u32x4 *)(p + c * 256);
+        x[4 * c] = q.x;
+        x[4 * c + 1] = q.y;
+        x[4 * c + 2] = q.z;
+        x[4 * c + 3] = q.w;
+    }
+}
+// From LDS, where a wave's unit keeps its order (p: this lane's first words).
+__device__ __forceinline__ void read_unit(u32 *x, const u32 *p) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const uint4 q = *(const uint4 *)(p + c * 256);
+        x[4 * c] = q.x;
+        x[4 * c + 1] = q.y;
+        x[4 * c + 2] = q.z;
+        x[4 * c + 3] = q.w;
+    }
+}
+// Four words of every lane to LDS, the wave's 1 KB from `to` on, without registers.
+__device__ __forceinline__ void load_to_lds(const u32 *from, u32 *to) {
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)from,
+                                     (__attribute__((address_space(3))) void *)to, 16, 0, 0);
+}
+constexpr int WAIT_LOADS = 0x0f70;  // s_waitcnt vmcnt(0), the other counters as they are
+__device__ __forceinline__ void store_unit(u32 *p, const u32 *x) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) *(uint4 *)(p + c * 256) = make_uint4(x[4 * c], x[4 * c + 1], x[4 * c + 2], x[4 * c + 3]);
+}
+
 // Forward: workgroup = slice of a group of X (its hx rows, zeros above) or of a window of
 // S (its hx + hz - 1 rows, at the top of the 2^P).
 template <int P>
@@ -1622,39 +1668,91 @@ k_gf2_rows_fwd(const Gf2Job *jobs, Gf2Job one, const uint2 *tab) {
         rows_exchange<P>(v, lds, own, own, [](u32 *l) { rows_basis<T_FWD, P>(l); });
     rows_stages<P, false>(v, lds, seed ? ~0u : 0u);
     // register rows are now rows 4 tid + b
-    u32 *out = (seed ? J.SB : J.XB) + ((uint64_t)(g * SLICES + sl) << (P + 4)) + threadIdx.x * 64;
+    u32 *out = (seed ? J.SB : J.XB) + ((uint64_t)(g * SLICES + sl) << (P + 4)) + unit_at(threadIdx.x);
 #pragma unroll
-    for (int k = 0; k < 64; k += 4) *(uint4 *)(out + k) = make_uint4(v[k], v[k + 1], v[k + 2], v[k + 3]);
+    for (int b = 0; b < 4; ++b) store_unit(out + b * UNIT, v + 16 * b);
 }
 
 // Sums of products of groups (more than one group of the input): a thread takes one row of
 // a slice in TG groups of z, whose seed windows it keeps in registers: the next input
-// group needs one new window, and the others shifted by one group.
+// group needs one new window, and the others shifted by one group. With TG = 4 the
+// registers hold two waves a SIMD (one wave alone issues an instruction in 5 clocks, two
+// in 2 each) and no operand ahead of its use, so the next input group's row and window
+// come straight into LDS while this one's products run. n = 2^30, m = 2^29 (32 groups by
+// 16): 1250 -> 640 us, of which the layout of the rows gave 120, the loads ahead 150 and
+// the second wave 340; the instructions alone are 380 us. Two turns ahead: 1005 against
+// 978 us before the second wave. TG = 1 (one group of z) reads 64 bytes for every product
+// and runs at 4.2 TB/s.
 template <int TG>
-__global__ void __launch_bounds__(256) k_gf2_rows_prod(const Gf2Job *jobs, Gf2Job one, const uint2 *tab) {
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TG > 1 ? 2 : 4))) k_gf2_rows_prod(const Gf2Job *jobs, Gf2Job one, const uint2 *tab) {
+    constexpr bool AHEAD = TG > 1;
+    __shared__ __align__(16) u32 lds[AHEAD ? 2 * 4 * 2 * UNIT : 4];  // two turns, four waves, row and window
     const uint2 tw = tab ? tab[blockIdx.x] : make_uint2(0, blockIdx.x);
     const Gf2Job &J = jobs ? jobs[tw.x] : one;
-    const u32 lg = J.rows_lg + 6, per = 1u << (lg - 8);  // rows of all slices of a group: 2^lg, `per` workgroups
-    const u32 g0 = tw.y / per * TG, nz = J.nz, nx = J.nx;
-    const uint64_t at = ((uint64_t)(tw.y % per) * 256 + threadIdx.x) * 16;
+    const u32 lg = J.rows_lg + 6;  // rows of all slices of a group: 2^lg, in 2^(lg - 8) workgroups
+    const u32 nz = J.nz, nx = J.nx;
+    // the tiles of z that read the same rows run side by side on one XCD (workgroups go to
+    // the eight XCDs in turn)
+    const u32 tiles = (nz + TG - 1) / TG, turn = tw.y >> 3;
+    const u32 g0 = turn % tiles * TG;
+    const u32 wave = (u32)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const uint64_t at = ((uint64_t)(turn / tiles * 8 + (tw.y & 7)) * 4 + wave) * UNIT + lane * 4;
+    const u32 *const XB = J.XB + at, *const SB = J.SB + at;
     u32 acc[TG][16] = {}, s[TG][16];
     // windows g0 + t + nx - 1 - q; before q = 0, those of t >= 1 in their places for t - 1
 #pragma unroll
     for (int t = 1; t < TG; ++t) {
         const u32 w = g0 + t + nx - 1;
-        load_slice(s[t - 1], J.SB + ((uint64_t)(w < nx + nz - 1 ? w : nx + nz - 2) << (lg + 4)) + at);
+        load_unit(s[t - 1], SB + ((uint64_t)(w < nx + nz - 1 ? w : nx + nz - 2) << (lg + 4)));
     }
+    auto place = [&](u32 q) { return lds + ((q & 1) * 4 + wave) * 2 * UNIT; };
+    auto fetch = [&](u32 q) {
+        const u32 *x = XB + ((uint64_t)q << (lg + 4)), *w = SB + ((uint64_t)(g0 + nx - 1 - q) << (lg + 4));
+        u32 *to = place(q);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            load_to_lds(x + c * 256, to + c * 256);
+            load_to_lds(w + c * 256, to + UNIT + c * 256);
+        }
+    };
+    if constexpr (AHEAD) fetch(0);
     for (u32 q0 = 0; q0 < nx; q0 += TG) {
 #pragma unroll
         for (int i = 0; i < TG; ++i) {  // (window of t at q0 + i: place (t - i - 1) mod TG)
             const u32 q = q0 + i;
             if (q >= nx) break;
             u32 x[16];
-            load_slice(x, J.XB + ((uint64_t)q << (lg + 4)) + at);
-            load_slice(s[(2 * TG - i - 1) % TG], J.SB + ((uint64_t)(g0 + nx - 1 - q) << (lg + 4)) + at);
+            if constexpr (AHEAD) {
+                // a wave reads only what it fetched itself; the other turn's place was read before
+                // the products of the turn before
+                __builtin_amdgcn_s_waitcnt(WAIT_LOADS);
+                const u32 *from = place(q) + lane * 4;
+                read_unit(x, from);
+                read_unit(s[(2 * TG - i - 1) % TG], from + UNIT);
+                // (read before the next fetch is begun, or the read would wait for that one)
+#pragma unroll
+                for (int k = 0; k < 16; ++k) asm volatile("" : "+v"(x[k]), "+v"(s[(2 * TG - i - 1) % TG][k]) : : "memory");
+                if (q + 1 < nx) fetch(q + 1);
+                step_end();
+            } else {
+                load_unit(x, XB + ((uint64_t)q << (lg + 4)));
+                load_unit(s[(2 * TG - i - 1) % TG], SB + ((uint64_t)(g0 + nx - 1 - q) << (lg + 4)));
+            }
+            // one 8-bit part of x for all windows, then the next: a third of its forms at a time
+            const PlaneForms f{x};
 #pragma unroll
             for (int t = 0; t < TG; ++t) {
-                mul16(acc[t], s[(2 * TG + t - i - 1) % TG], PlaneForms{x});
+                mul16_low(acc[t], s[(2 * TG + t - i - 1) % TG], f);
+                step_end();
+            }
+#pragma unroll
+            for (int t = 0; t < TG; ++t) {
+                mul16_sum(acc[t], s[(2 * TG + t - i - 1) % TG], f);
+                step_end();
+            }
+#pragma unroll
+            for (int t = 0; t < TG; ++t) {
+                mul8<2>(acc[t], s[(2 * TG + t - i - 1) % TG] + 8, f);
                 step_end();
             }
         }
@@ -1662,9 +1760,7 @@ __global__ void __launch_bounds__(256) k_gf2_rows_prod(const Gf2Job *jobs, Gf2Jo
 #pragma unroll
     for (int t = 0; t < TG; ++t) {
         if (g0 + t >= nz) break;
-        u32 *out = J.PB + ((uint64_t)(g0 + t) << (lg + 4)) + at;
-#pragma unroll
-        for (int k = 0; k < 16; k += 4) *(uint4 *)(out + k) = make_uint4(acc[t][k], acc[t][k + 1], acc[t][k + 2], acc[t][k + 3]);
+        store_unit(J.PB + ((uint64_t)(g0 + t) << (lg + 4)) + at, acc[t]);
     }
 }
 
@@ -1678,18 +1774,20 @@ k_gf2_rows_inv(const Gf2Job *jobs, Gf2Job one, const uint2 *tab) {
     __shared__ __align__(16) u32 lds[Rw::LDS_WORDS];
     const uint2 tw = tab ? tab[blockIdx.x] : make_uint2(0, blockIdx.x);
     const Gf2Job &J = jobs ? jobs[tw.x] : one;
-    const u32 sl = tw.y / J.nz, g = tw.y % J.nz;
+    // slices side by side on one XCD (workgroups go to the eight in turn): the 64-byte halves
+    // of a line of G meet in its L2
+    const u32 r0 = tw.y % SLICES, sl = (r0 & 7) * 8 + (r0 >> 3), g = tw.y / SLICES;
     u32 v[64];
-    const uint64_t at = ((uint64_t)(g * SLICES + sl) << (P + 4)) + threadIdx.x * 64;
+    const uint64_t at = ((uint64_t)(g * SLICES + sl) << (P + 4)) + unit_at(threadIdx.x);
     if (J.nx > 1) {
 #pragma unroll
-        for (int b = 0; b < 4; ++b) load_slice(v + 16 * b, J.PB + at + 16 * b);
+        for (int b = 0; b < 4; ++b) load_unit(v + 16 * b, J.PB + at + b * UNIT);
     } else {  // (then nz is 1 as well)
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
             u32 a[16], c[16];
-            load_slice(a, J.XB + at + 16 * b);
-            load_slice(c, J.SB + at + 16 * b);
+            load_unit(a, J.XB + at + b * UNIT);
+            load_unit(c, J.SB + at + b * UNIT);
 #pragma unroll
             for (int e = 0; e < 16; ++e) v[16 * b + e] = 0u;
             mul16(v + 16 * b, a, PlaneForms{c});

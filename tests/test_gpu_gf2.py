@@ -111,6 +111,13 @@ def test_products_by_a_transform_over_rows(ctx, n, m, order):
     _check(ctx, "toeplitz", n, m, order, rows=True)
 
 
+@pytest.mark.parametrize("nx,nz", [(2, 2), (3, 2), (4, 4), (5, 3), (6, 5)])
+def test_sums_of_products_of_groups(ctx, nx, nz):
+    """Groups of 2048 rows, whose products are summed four groups of the output at a time, the
+    next turn's input fetched ahead: the fewest turns, and tiles that are not full."""
+    _check(ctx, "toeplitz", (2048 * (nx - 1) + 1) * B - 3, (2048 * (nz - 1) + 1) * B - 7, "paper", rows=True)
+
+
 @pytest.mark.parametrize("kind,n,m", [("dodis", 16421, 9000), ("dodis", 65587, 65587), ("circulant", 16420, 16420),
                                       ("circulant", 65586, 30001), ("dodis", 1048589, 1 << 19),
                                       ("circulant", 3145748, 3145748)])
