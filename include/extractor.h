@@ -75,11 +75,20 @@ extern "C" {
  * with near-perfect seeds used t times); the cache is keyed by the seed pointer and the
  * shape (kind, n, m, seed order), so the caller must not change the seed bits
  * at that address while they are cached (ext_seed_cache_clear drops them).
- * A hit skips one of the three transforms. Sizes that run in one workgroup
- * and the piece schedules (see EXT_SINGLE_TRANSFORM) ignore the flag. */
+ * A hit skips one of the three transforms. The flag keeps the number-theoretic
+ * transform where the default would be products over GF(2)[t] (see
+ * EXT_SINGLE_TRANSFORM). Sizes that run in one workgroup and the piece schedules
+ * ignore the flag. */
 #define EXT_SEED_CACHED 8u
-/* Single calls: compute the extraction as one transform even where the
- * two-piece schedule applies. By default an extraction whose single transform
+/* Single calls: compute the extraction as one number-theoretic transform.
+ * By default most extractions are products over GF(2)[t] (bits in, bits out: short
+ * ones bit by bit, single calls with n + m - 1 > 2^20 and batch members by additive
+ * FFTs in bit planes), wherever their workspace is no larger than the transform's
+ * (up to about 2^35 bits). The transform serves the other single calls, this flag,
+ * EXT_SEED_CACHED, size classes whose plan the caller has set on this context
+ * (ext_tune_set, ext_tune_set_single) and the larger shapes; every route gives the
+ * same bits. Without this flag a transform is split into pieces where that is
+ * faster: an extraction whose single transform
  * would need the 64-bit field (n + m - 1 > 2^30; for Dodis and Circulant n is
  * the circulant length) while halves of the input fit transforms of at most
  * 2^30 runs as two pieces over 3*2^30+1: the sum over input positions that
@@ -197,7 +206,8 @@ typedef struct ext_job {
 
 /* Run many independent extractions (the paper's many privacy-amplification
  * blocks, section "Cryptomite for privacy amplification in QKD") as a few
- * grouped launches: jobs are grouped by transform size; all single-workgroup
+ * grouped launches. Jobs on the GF(2)[t] route share its launches; the others are
+ * grouped by transform size: all single-workgroup
  * sizes (transform length <= 2^14) run in one persistent launch that takes
  * jobs from a work counter, larger sizes as batched multi-pass launches, one
  * set per size class. Jobs whose single call would run a piece schedule (see
@@ -217,13 +227,13 @@ int extract_batch_unbatched(ext_ctx *ctx, ext_job *jobs, size_t count, uint32_t 
 
 /* ---- sizes, memory, utilities --------------------------------------- */
 
-/* Device workspace bytes one extraction of this shape takes from the pool
- * (0 if the shape is invalid). kind: EXT_KIND_*; n as for the calls (m is
+/* Device workspace bytes one extraction of this shape takes from the pool at most
+ * (those of its transform; the GF(2)[t] route takes no more; 0 if the shape is invalid). kind: EXT_KIND_*; n as for the calls (m is
  * ignored for EXT_KIND_VON_NEUMANN). */
 size_t ext_workspace_bytes(int32_t kind, uint64_t n, uint64_t m);
 
-/* Transform length L and field (32 or 64 = word bits) chosen for a shape by
- * default (for a piece schedule: the length of each piece's transforms);
+/* Transform length L and field (32 or 64 = word bits) of a shape's number-theoretic
+ * transform (for a piece schedule: the length of each piece's transforms);
  * 0 on error. */
 uint64_t ext_plan_length(int32_t kind, uint64_t n, uint64_t m, int32_t *word_bits);
 
@@ -243,8 +253,9 @@ int ext_seed_cache_clear(ext_ctx *ctx, size_t *bytes, size_t *entries);
  * nlev = 0 runs each job in one workgroup (32-bit field, lg <= 14); nlev >= 2
  * gives the log2 sizes of the passes, lgr[0..nlev-2] the strided ones and
  * lgr[nlev-1] the contiguous one (sum = lg, each within the compiled tile
- * sizes). ext_tune_set overrides the built-in plan for later calls (nlev < 0
- * removes the override); EXT_EINVAL for an unsupported plan. ext_tune_get
+ * sizes). ext_tune_set overrides the built-in plan for later calls, which then run
+ * that transform (nlev < 0 removes the override; plans of a tuning file given to
+ * ext_create do not choose the route); EXT_EINVAL for an unsupported plan. ext_tune_get
  * reports the plan in use. These plans serve batches (extract_batch), and single
  * calls whose size class has no single-call plan.
  * ext_tune_set_single / ext_tune_get_single: the plan of single extraction

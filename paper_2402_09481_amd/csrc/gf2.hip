@@ -983,7 +983,10 @@ __device__ inline void degen_part(const Gf2Job &J, u32 g, u32 *red) {
 // Forward transforms: workgroup `wg` of the job takes 8 rows, two to a wave: the input's px
 // rows (an odd count padded by an idle one), then the ps seed windows; the workgroups
 // after those run the Dodis check. tab: per workgroup its job and its number within
-// the job (nullptr: the one job).
+// the job (nullptr: the one job). Bound by instruction issue: 5361 instructions a wave of
+// two rows, 17.8 us where each SIMD has one wave (a lone wave issues one in 7 clocks: n =
+// 2^20) and 660 us for the 163839 rows of n = 2^30, m = 2^29. 113 registers hold four
+// waves a SIMD; five or six waves spill 59 or 125 registers.
 __global__ void __launch_bounds__(64 * FWD_WAVES) __attribute__((amdgpu_waves_per_eu(4))) k_gf2_fwd(const Gf2Job *jobs, Gf2Job one, const uint2 *tab) {
     __shared__ __align__(16) u32 lds_all[FWD_WAVES * 2 * ROW_LDS];
     const uint2 tw = tab ? tab[blockIdx.x] : make_uint2(0, blockIdx.x);
@@ -1118,6 +1121,8 @@ __device__ __forceinline__ void load_slice(u32 *x, const u32 *slice) {
 
 // Product rows: G[split][r] = sum of X_q S_(r-q+px-1) over the split's q. A wave takes
 // every (8 splits)-th q, a lane 32 values of the row; the eight waves' sums meet in LDS.
+// About 260 instructions a product; latency at one call's sizes (6 us at n = 2^20, m =
+// 2^19, 13 us at n = 2^21, m = 2^20), instruction issue in a batch.
 constexpr int MUL_WAVES = 8;
 __global__ void __launch_bounds__(64 * MUL_WAVES) k_gf2_mul(const Gf2Job *jobs, Gf2Job one, const uint2 *tab) {
     __shared__ __align__(16) u32 part[MUL_WAVES * ROW_WORDS];
@@ -1615,7 +1620,11 @@ __device__ __forceinline__ void store_unit(u32 *p, const u32 *x) {
 }
 
 // Forward: workgroup = slice of a group of X (its hx rows, zeros above) or of a window of
-// S (its hx + hz - 1 rows, at the top of the 2^P).
+// S (its hx + hz - 1 rows, at the top of the 2^P). With P = 12 one workgroup fills a CU's
+// registers and LDS: 5056 workgroups (n = 2^30, m = 2^29) take 1170 us, 59 us a round,
+// of which the 7150 instructions a wave are 30 and the 256 KB in and out the rest, not
+// overlapped. The larger P is still the cheaper: half of it would double the sums of
+// products.
 template <int P>
 __global__ void __launch_bounds__(Rows<P>::NT) __attribute__((amdgpu_waves_per_eu(P == 12 ? 4 : 1)))
 k_gf2_rows_fwd(const Gf2Job *jobs, Gf2Job one, const uint2 *tab) {
@@ -1766,7 +1775,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TG > 1
 
 // Backwards: workgroup = slice of a group of z: its product (or, with several groups of the
 // input, the sum that k_gf2_rows_prod left), the transform back, and its rows (in reverse
-// order) to G.
+// order) to G. Bound like k_gf2_rows_fwd: 245 us for 1024 workgroups of P = 12.
 template <int P>
 __global__ void __launch_bounds__(Rows<P>::NT) __attribute__((amdgpu_waves_per_eu(P == 12 ? 4 : 1)))
 k_gf2_rows_inv(const Gf2Job *jobs, Gf2Job one, const uint2 *tab) {
@@ -1812,7 +1821,8 @@ k_gf2_rows_inv(const Gf2Job *jobs, Gf2Job one, const uint2 *tab) {
 
 // Backwards transforms of the product rows and the output bits: 8 rows to a workgroup,
 // two to a wave. Output block r is in reverse order: position i of the row is z bit
-// r B + B - 1 - i.
+// r B + B - 1 - i. Bound like k_gf2_fwd: 15.4 us with one wave a SIMD, 140 us for the 32768
+// rows of n = 2^30, m = 2^29.
 __global__ void __launch_bounds__(64 * FWD_WAVES) __attribute__((amdgpu_waves_per_eu(4))) k_gf2_inv(const Gf2Job *jobs, Gf2Job one, const uint2 *tab) {
     __shared__ __align__(16) u32 lds_all[FWD_WAVES * 2 * ROW_LDS];
     const uint2 tw = tab ? tab[blockIdx.x] : make_uint2(0, blockIdx.x);
@@ -1878,7 +1888,9 @@ __global__ void __launch_bounds__(64 * FWD_WAVES) __attribute__((amdgpu_waves_pe
 // outputs, and one AND-XOR adds them: 3 instructions (with the bit's mask) for 32
 // products, no passes and no workspace. A workgroup takes OW output words and the
 // whole input; a lane takes one output word and a share of the input words (the seed
-// window of the next input word is the last one's, moved by a word).
+// window of the next input word is the last one's, moved by a word). Circulant n = 16420,
+// m = 9000: 6.2 us a call, where the transform's five launches took 26; Toeplitz n = 4096,
+// m = 2048, with the wait for it, 32.2 -> 17 us.
 constexpr int BITS_NT = 512;
 
 template <int OW>
