@@ -523,6 +523,7 @@ struct ext_ctx {
         hipGraphExec_t exec = nullptr;
         char *desc_dev = nullptr;
         char *desc_host[2] = {nullptr, nullptr};  // pinned
+        size_t staged = 0;  // bytes of descriptors and tables the three were made for
         hipEvent_t done[2] = {nullptr, nullptr};
         bool used[2] = {false, false};
         int next = 0;
@@ -1946,6 +1947,14 @@ struct BatchLayout {
     struct Gf2Chunk {
         size_t first, n;
         Gf2Launch bits, fwd, mul, inv, prod[2], rows_fwd[gf2::ROWS_LG_MAX + 1], rows_inv[gf2::ROWS_LG_MAX + 1];
+        template <class F>
+        void each(F &&f) {  // every launch
+            for (Gf2Launch *l : {&bits, &fwd, &mul, &inv, &prod[0], &prod[1]}) f(*l);
+            for (int p = gf2::ROWS_LG_MIN; p <= gf2::ROWS_LG_MAX; ++p) {
+                f(rows_fwd[p]);
+                f(rows_inv[p]);
+            }
+        }
     };
     std::vector<Gf2Chunk> gf2_chunks;
     size_t ntab = 0;
@@ -1987,28 +1996,14 @@ void layout_gf2(const std::vector<Member> &members, size_t cap, BatchLayout &bl)
         }
         ch.n = i - ch.first;
         bl.max_ws = std::max(bl.max_ws, ws);
-        char b[96];
-        snprintf(b, sizeof b, "g%zu:%u:%u:%u:%u", ch.n, ch.bits.wgs, ch.fwd.wgs, ch.mul.wgs, ch.inv.wgs);
-        bl.sig += b;
-        auto place = [&](BatchLayout::Gf2Launch &l) {
+        // the signature names the size of every launch: with them the tables' places and the
+        // staged block's size are the same for all batches that replay one graph
+        bl.sig += "g" + std::to_string(ch.n);
+        ch.each([&](BatchLayout::Gf2Launch &l) {
             l.tab = bl.ntab;
             bl.ntab += l.wgs;
-        };
-        place(ch.bits);
-        place(ch.fwd);
-        place(ch.mul);
-        place(ch.inv);
-        for (auto &l : ch.prod) {
-            place(l);
-            snprintf(b, sizeof b, ":%u", l.wgs);
-            bl.sig += b;
-        }
-        for (int p = gf2::ROWS_LG_MIN; p <= gf2::ROWS_LG_MAX; ++p) {
-            place(ch.rows_fwd[p]);
-            place(ch.rows_inv[p]);
-            snprintf(b, sizeof b, ":%u", ch.rows_fwd[p].wgs);
-            bl.sig += b;
-        }
+            bl.sig += ":" + std::to_string(l.wgs);
+        });
         bl.sig += "|";
         bl.gf2_chunks.push_back(ch);
     }
@@ -2306,6 +2301,7 @@ extern "C" int extract_batch(ext_ctx *c, ext_job *jobs, size_t count, uint32_t f
             ge = &c->graphs[bl.sig];
         }
         if (!ge->desc_dev) {
+            ge->staged = staged;
             bool ok = hipMalloc((void **)&ge->desc_dev, desc_bytes + 256) == hipSuccess &&
                       hipEventCreateWithFlags(&ge->replayed, hipEventDisableTiming) == hipSuccess;
             for (int k = 0; k < 2 && ok; ++k)
@@ -2315,6 +2311,10 @@ extern "C" int extract_batch(ext_ctx *c, ext_job *jobs, size_t count, uint32_t f
                 pool_release(c, lease, stream);
                 return EXT_EDEVICE;
             }
+        }
+        if (ge->staged != staged) {  // (the signature determines it)
+            pool_release(c, lease, stream);
+            return EXT_EDEVICE;
         }
         uint32_t *counter = (uint32_t *)(ge->desc_dev + desc_bytes);
         // this staging buffer may still be read by the copy of the replay before last

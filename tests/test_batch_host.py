@@ -1,0 +1,99 @@
+"""Batches on the CPU: the C-ABI's own host code (csrc/abi.cpp) on a model of the HIP
+calls (tests/abi_host), every launch checked for the workgroups of every job. A graph
+recorded for one batch is replayed only for batches of the same launches."""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+PKG = os.path.join(os.path.dirname(HERE), "paper_2402_09481_amd")
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+GRAPH = 4
+B = 1 << 14
+
+
+class Result:
+    pass
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    if not os.path.exists(HIPCC):
+        pytest.skip("hipcc not available")
+    out = str(tmp_path_factory.mktemp("abi") / "abi_host.so")
+    # (-Bsymbolic: the model's HIP calls, not the runtime's)
+    subprocess.check_call([HIPCC, "--offload-arch=gfx950", "--offload-host-only", "-x", "hip", "-O1", "-std=c++17", "-shared", "-fPIC",
+                           "-Wno-unused-value", "-Wno-unused-result", os.path.join(HERE, "abi_host", "abi_host.cpp"), "-o", out,
+                           "-Wl,-Bsymbolic", "-L" + PKG, "-Wl,-rpath," + PKG, "-l:libextractor.so"])
+    L = ctypes.CDLL(out)
+    L.host_ctx.restype = ctypes.c_void_p
+    L.host_ctx.argtypes = [ctypes.c_size_t, ctypes.c_int]
+    L.host_ctx_free.argtypes = [ctypes.c_void_p]
+    L.host_batch.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_uint32] + [ctypes.c_void_p] * 4 + \
+        [ctypes.c_char_p, ctypes.c_size_t]
+    return L
+
+
+@pytest.fixture
+def context(lib):
+    made = []
+
+    def make(budget=256 << 30, gf2=True):
+        made.append(lib.host_ctx(budget, int(gf2)))
+        return made[-1]
+    yield make
+    for c in made:
+        lib.host_ctx_free(c)
+
+
+def run(lib, c, jobs, graph=False):
+    """jobs: (kind, n, m) rows"""
+    a = np.ascontiguousarray(jobs, np.uint64)
+    r = Result()
+    faults, done, threads, leased = ctypes.c_int(), ctypes.c_size_t(), ctypes.c_uint64(), ctypes.c_size_t()
+    labels = ctypes.create_string_buffer(1 << 13)
+    r.rc = lib.host_batch(c, a.ctypes.data, len(a), GRAPH if graph else 0, ctypes.byref(faults), ctypes.byref(done),
+                          ctypes.byref(threads), ctypes.byref(leased), labels, len(labels))
+    r.faults, r.done, r.threads, r.leased = faults.value, done.value, threads.value, leased.value
+    r.labels = labels.value.decode().split()
+    return r
+
+
+def toeplitz(*shapes):
+    return [(0, n, m) for n, m in shapes]
+
+
+# batches of three whose launches differ in the transforms back over rows alone
+ALIKE = [
+    (toeplitz((100679680, 66994176), (100663296, 67108864), (100663296, 67108864)),
+     toeplitz((100663296, 67239936), (100663296, 67239936), (100663296, 66846720))),
+    (toeplitz(*((n * B, m * B) for n, m in ((5144, 4065), (7501, 1894), (6897, 5313)))),
+     toeplitz(*((n * B, m * B) for n, m in ((8828, 6257), (5037, 642), (5673, 4376))))),
+]
+
+
+@pytest.mark.parametrize("first,second", [(p[i], p[1 - i]) for p in ALIKE for i in (0, 1)])
+def test_replays_of_batches_with_nearly_the_same_launches(lib, context, first, second):
+    c = context()
+    for jobs in (first, second, first):
+        r = run(lib, c, jobs, graph=True)
+        assert r.rc == 0 and r.faults == 0 and r.done == len(jobs), (r.rc, r.faults, r.done)
+
+
+@pytest.mark.parametrize("graph", [False, True])
+def test_every_workgroup_of_mixed_batches(lib, context, graph):
+    """Every step, number of rows and number of groups, many batches through one context."""
+    c = context()
+    g = np.random.default_rng(7)
+    for _ in range(40):
+        count = int(g.integers(1, 7))
+        jobs = []
+        for _ in range(count):
+            n = int(2 ** g.uniform(3, 27.5))
+            jobs.append((0, n, max(1, int(n * 2 ** g.uniform(-5, 0)))))
+        r = run(lib, c, jobs, graph)
+        assert r.rc == 0 and r.faults == 0, jobs
+        assert r.done == count or "strided" in r.labels or "small" in r.labels, jobs
