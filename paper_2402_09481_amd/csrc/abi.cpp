@@ -1966,6 +1966,11 @@ struct BatchLayout {
     size_t staged_bytes() const { return tab_offset() + ntab * sizeof(uint2); }
 };
 
+// Workgroups of a chunk's launch at most: with the 1024 threads of the widest kernel half of
+// the 2^32 that a grid may have, and 16 MiB of table. (No single job has as many: 1.1 million
+// at n = 2^36.)
+constexpr uint32_t GF2_LAUNCH_MAX = uint32_t(1) << 21;
+
 void layout_gf2(const std::vector<Member> &members, size_t cap, BatchLayout &bl) {
     for (auto &mb : members)
         if (mb.gf2) bl.gf2.push_back(&mb);
@@ -1975,24 +1980,33 @@ void layout_gf2(const std::vector<Member> &members, size_t cap, BatchLayout &bl)
         BatchLayout::Gf2Chunk ch{};
         ch.first = i;
         size_t ws = 0;
-        auto add = [](BatchLayout::Gf2Launch &l, uint32_t wgs) { l.wgs += wgs; };
         for (; i < bl.gf2.size() && (i == ch.first || ws + bl.gf2[i]->gp.total <= cap); ++i) {
             const Member &mb = *bl.gf2[i];
-            ws += align256(mb.gp.total);
             const Gf2Job j = gf2_job(mb.shape, mb.gp, nullptr, nullptr, nullptr, nullptr, 0, nullptr);
+            struct {
+                BatchLayout::Gf2Launch *launch;
+                uint32_t wgs;
+            } part[5];
+            int parts = 0;
+            auto add = [&](BatchLayout::Gf2Launch &l, uint32_t wgs) { part[parts++] = {&l, wgs}; };
             if (mb.gp.bits) {
                 add(ch.bits, gf2_bits_workgroups(j, true));
-                continue;
-            }
-            add(ch.fwd, gf2_fwd_workgroups(j));
-            if (j.rows_lg) {
-                add(ch.rows_fwd[j.rows_lg], gf2_rows_fwd_workgroups(j));
-                add(ch.prod[j.nz == 1], gf2_rows_prod_workgroups(j));
-                add(ch.rows_inv[j.rows_lg], gf2_rows_inv_workgroups(j));
             } else {
-                add(ch.mul, gf2_mul_workgroups(j));
+                add(ch.fwd, gf2_fwd_workgroups(j));
+                if (j.rows_lg) {
+                    add(ch.rows_fwd[j.rows_lg], gf2_rows_fwd_workgroups(j));
+                    add(ch.prod[j.nz == 1], gf2_rows_prod_workgroups(j));
+                    add(ch.rows_inv[j.rows_lg], gf2_rows_inv_workgroups(j));
+                } else {
+                    add(ch.mul, gf2_mul_workgroups(j));
+                }
+                add(ch.inv, gf2_inv_workgroups(j));
             }
-            add(ch.inv, gf2_inv_workgroups(j));
+            bool fits = true;
+            for (int k = 0; k < parts; ++k) fits = fits && part[k].launch->wgs + part[k].wgs <= GF2_LAUNCH_MAX;
+            if (!fits && i > ch.first) break;
+            for (int k = 0; k < parts; ++k) part[k].launch->wgs += part[k].wgs;
+            ws += align256(mb.gp.total);
         }
         ch.n = i - ch.first;
         bl.max_ws = std::max(bl.max_ws, ws);

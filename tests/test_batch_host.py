@@ -97,3 +97,11 @@ def test_every_workgroup_of_mixed_batches(lib, context, graph):
         r = run(lib, c, jobs, graph)
         assert r.rc == 0 and r.faults == 0, jobs
         assert r.done == count or "strided" in r.labels or "small" in r.labels, jobs
+
+
+def test_launches_stay_within_a_grid(lib, context):
+    """A launch holds fewer than 2^32 threads, however many short members a batch has: 524,289
+    members of 8192 output bits are 2^23 + 16 workgroups of 512 threads."""
+    r = run(lib, context(), np.tile(np.array([0, 8192, 8192], np.uint64), ((1 << 19) + 1, 1)))
+    assert r.rc == 0 and r.faults == 0 and r.done == (1 << 19) + 1
+    assert r.threads < 1 << 32
