@@ -2292,12 +2292,32 @@ extern "C" int extract_batch(ext_ctx *c, ext_job *jobs, size_t count, uint32_t f
     if (members.empty()) return first;
     BatchLayout bl;
     layout_batch(c, members, bl);
-    const size_t staged = bl.staged_bytes(), desc_bytes = align256(staged);
+    size_t staged = 0, desc_bytes = 0;
+    // The batch's workspace; without a graph, its descriptors and the work counter before it. A
+    // batch on the GF(2)[t] route mostly takes far less than on the transforms, but more where
+    // descriptors and tables are all there is (4096 members of 8192 bits: 1.6 MB against
+    // 1.0): what held the transforms holds the batch, on them.
+    auto lease_batch = [&](Lease &lease) {
+        for (bool again = false;; again = true) {
+            staged = bl.staged_bytes();
+            desc_bytes = align256(staged);
+            const int rc = pool_acquire(c, (flags & EXT_GRAPH ? 0 : desc_bytes + 256) + bl.max_ws, stream, lease);
+            if (rc != EXT_ENOMEM || again || bl.gf2.empty()) return rc;
+            for (Member &mb : members) {
+                if (!mb.gf2) continue;
+                mb.gf2 = false;
+                const int prc = plan_shape(c, mb.shape, mb.plan, jobs[mb.job].flags, true);
+                if (prc != EXT_OK) return prc;
+            }
+            bl = BatchLayout();
+            layout_batch(c, members, bl);
+        }
+    };
     hipError_t e = hipSuccess;
     if (flags & EXT_GRAPH) {
         std::lock_guard<std::mutex> graph_lock(c->graph_mu);
         Lease lease;
-        int rc = pool_acquire(c, bl.max_ws, stream, lease);
+        int rc = lease_batch(lease);
         if (rc != EXT_OK) return rc;
         ext_ctx::GraphEntry *ge;
         {
@@ -2365,7 +2385,7 @@ extern "C" int extract_batch(ext_ctx *c, ext_job *jobs, size_t count, uint32_t f
     } else {
         // descriptors and the work counter live at the front of the leased workspace
         Lease lease;
-        int rc = pool_acquire(c, desc_bytes + 256 + bl.max_ws, stream, lease);
+        int rc = lease_batch(lease);
         if (rc != EXT_OK) return rc;
         Pinned pin;
         char *host = pinned_take(c, staged, pin);

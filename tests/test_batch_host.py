@@ -105,3 +105,27 @@ def test_launches_stay_within_a_grid(lib, context):
     r = run(lib, context(), np.tile(np.array([0, 8192, 8192], np.uint64), ((1 << 19) + 1, 1)))
     assert r.rc == 0 and r.faults == 0 and r.done == (1 << 19) + 1
     assert r.threads < 1 << 32
+
+
+def _classes(lo, hi, count):
+    """as many members of every transform length as fill a workspace of about `count` of the largest"""
+    return toeplitz(*((1 << (lg - 1), 1 << (lg - 2)) for lg in range(lo, hi) for _ in range(count << (hi - 1 - lg))))
+
+
+@pytest.mark.parametrize("graph", [False, True])
+@pytest.mark.parametrize("name,jobs", [
+    ("short", toeplitz(*[(8192, 8192)] * 4096)),
+    ("one class", toeplitz(*[(1 << 18, 1 << 17)] * 64)),
+    ("classes", _classes(15, 29, 1)),
+    ("long inputs, short outputs", toeplitz(*[(n, 64) for n in range(1 << 15, 1 << 20, 1 << 13)])),
+])
+def test_a_budget_that_held_the_transforms_holds_the_batch(lib, context, name, jobs, graph):
+    """Workspace and descriptors of the members on their transforms: as much is enough on any route."""
+    r = run(lib, context(gf2=False), jobs, graph)
+    assert r.rc == 0 and r.done == 0
+    c = context(budget=r.leased)
+    for _ in range(2):
+        r = run(lib, c, jobs, graph)
+        assert r.rc == 0 and r.faults == 0, (name, r.rc)
+    r = run(lib, context(budget=r.leased // 2), jobs, graph)  # (less may be enough, or is refused)
+    assert r.rc in (0, -4)
