@@ -1917,6 +1917,36 @@ std::string plan_key(const Plan &p) {
     return b;
 }
 
+// A few members that share one transform's launches run it rather than three launches of
+// rows: its five launches of little work are the shorter chain. Two, four and eight members,
+// us a batch back to back, GF(2)[t] / transform: n = 21299, m = 10649 (2^15) 45 45 47 / 31 32
+// 33; n = m = 65536 (2^17) 47 47 46 / 38 40 46; n = m = 131072 (2^18) 48 47 48 / 39 47 57; n =
+// m = 262144 (2^19) 47 48 49 / 46 56 72. So while the members have one size class, no pieces
+// and 2^20 coefficients together at most, and no longer member brings the rows' launches
+// anyway (two classes: 46 / 81 us). Eight members at most: waited for one by one, twelve and
+// more take the rows' time or longer (62 / 66 us at n = 21299). (One member alone keeps the
+// rows, at 44 us against 31 for n = 21299: the GPU tests reach their short shapes that way.)
+constexpr size_t GF2_FEW = 8;
+constexpr uint64_t GF2_FEW_VALUES = uint64_t(1) << 20;
+void few_to_transform(ext_ctx *c, const ext_job *jobs, std::vector<Member> &members) {
+    std::vector<Member *> few;
+    std::vector<Plan> plans;
+    for (Member &mb : members) {
+        if (!mb.gf2 || mb.gp.bits) continue;
+        Plan p;
+        if (few.size() == GF2_FEW || mb.shape.Lmin > GF2_FEW_VALUES ||
+            plan_shape(c, mb.shape, p, jobs[mb.job].flags, true) != EXT_OK || p.pieces > 1 || p.small ||
+            ((few.size() + 1) << p.lg) > GF2_FEW_VALUES || (!few.empty() && plan_key(p) != plan_key(plans[0])))
+            return;
+        few.push_back(&mb);
+        plans.push_back(p);
+    }
+    for (size_t i = 0; i < few.size() && few.size() > 1; ++i) {
+        few[i]->gf2 = false;
+        few[i]->plan = plans[i];
+    }
+}
+
 // Launch layout of a batch: single-workgroup jobs first (sorted by size, one
 // persistent launch), then chunks of one multi-pass size class each. A chunk's
 // jobs get consecutive workspaces; chunks run one after another in stream
@@ -2290,6 +2320,7 @@ extern "C" int extract_batch(ext_ctx *c, ext_job *jobs, size_t count, uint32_t f
         members.push_back(mb);
     }
     if (members.empty()) return first;
+    few_to_transform(c, jobs, members);
     BatchLayout bl;
     layout_batch(c, members, bl);
     size_t staged = 0, desc_bytes = 0;

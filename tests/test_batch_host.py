@@ -129,3 +129,28 @@ def test_a_budget_that_held_the_transforms_holds_the_batch(lib, context, name, j
         assert r.rc == 0 and r.faults == 0, (name, r.rc)
     r = run(lib, context(budget=r.leased // 2), jobs, graph)  # (less may be enough, or is refused)
     assert r.rc in (0, -4)
+
+
+@pytest.mark.parametrize("graph", [False, True])
+@pytest.mark.parametrize("jobs,transform", [
+    ([(21299, 10649)] * 2, True),
+    ([(21299, 10649)] * 8, True),
+    ([(21299, 10649)] * 9, False),
+    ([(65536, 65536)] * 8, True),
+    ([(131072, 131072)] * 4, True),
+    ([(131072, 131072)] * 5, False),                # more than 2^20 coefficients
+    ([(340787, 170393)] * 2, True),
+    ([(524288, 524288)] * 2, False),
+    ([(85196, 5324)] * 2, False),                   # (as transforms two pieces each)
+    ([(21299, 10649), (42598, 21299)], False),      # two transform lengths
+    ([(85196, 42598)] * 2 + [(1 << 21, 1 << 20)], False),  # beside a member of the other route
+    ([(85196, 42598)] * 2 + [(4096, 2048)] * 3, True),     # beside short members
+    ([(85196, 42598)], False),
+])
+def test_few_members_of_one_length_share_a_transform(lib, context, jobs, transform, graph):
+    """Two to eight members of one transform length, 2^20 coefficients together at most."""
+    r = run(lib, context(), toeplitz(*jobs), graph)
+    assert r.rc == 0 and r.faults == 0
+    short = sum(n + m - 1 <= 1 << 14 for n, m in jobs)
+    assert ("strided" in r.labels, "fwd" in r.labels) == (transform, not transform), r.labels
+    assert r.done == (short if transform else len(jobs))
