@@ -258,12 +258,12 @@ class Context:
         the launch sequence of this batch signature into a HIP graph and replays it."""
         arr = (ExtJob * len(jobs))()
         marshal = _lib.marshal()
-        if not marshal.fill(jobs, ctypes.addressof(arr)):  # a job of another than the ordinary form
+        if marshal is None or not marshal.fill(jobs, ctypes.addressof(arr)):  # (a job of another than the ordinary form)
             self._fill_jobs(jobs, arr)
         fn = self._lib.extract_batch_unbatched if unbatched else self._lib.extract_batch
         flags = (EXT_SYNC if sync else 0) | (_lib.EXT_GRAPH if (graph and not unbatched) else 0)
         rc = fn(self.handle, arr, len(jobs), flags, _stream_handle(stream, self.device))
-        return rc, marshal.errs(ctypes.addressof(arr), len(jobs))
+        return rc, [j.err for j in arr] if marshal is None else marshal.errs(ctypes.addressof(arr), len(jobs))
 
     @staticmethod
     def _fill_jobs(jobs, arr):

@@ -7,6 +7,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 SO_PATH = os.path.join(HERE, "libextractor.so")
@@ -136,24 +137,31 @@ def load() -> ctypes.CDLL:
     return lib
 
 
-_marshal = None
+# The host module that fills a batch's job array (csrc/marshal.cpp), for this Python.
+MARSHAL_PATH = os.path.join(HERE, "_marshal" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
+_marshal = None  # the module once it is loaded, False where it is not to be used
 
 
 def marshal():
-    """The host module that fills a batch's job array (csrc/marshal.cpp)."""
+    """That module, or None where there is none built for this Python and torch (the binding
+    then fills the array itself)."""
     global _marshal
     if _marshal is None:
         import importlib.machinery
         import importlib.util
-        path = os.path.join(HERE, "_marshal.so")
-        if not os.path.exists(path):
-            raise ImportError("_marshal.so is not built (%s). Build it with `python -m paper_2402_09481_amd.build`." % path)
-        import torch  # noqa: F401  (its libraries are the module's)
-        loader = importlib.machinery.ExtensionFileLoader("_marshal", path)
-        mod = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_marshal", path, loader=loader))
-        loader.exec_module(mod)
+
+        import torch  # (its libraries are the module's)
+        mod = False
+        try:
+            loader = importlib.machinery.ExtensionFileLoader("_marshal", MARSHAL_PATH)
+            mod = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_marshal", MARSHAL_PATH, loader=loader))
+            loader.exec_module(mod)
+            if mod.torch != torch.__version__:  # its view of a tensor is that version's
+                mod = False
+        except (ImportError, OSError, AttributeError):
+            mod = False
         _marshal = mod
-    return _marshal
+    return _marshal or None
 
 
 def strerror(code: int) -> str:

@@ -1,4 +1,4 @@
-"""Build libextractor.so (gfx950) in-tree with hipcc, and the host module _marshal.so.
+"""Build libextractor.so (gfx950) in-tree with hipcc, and the host module _marshal.
 
 The transform kernel file is compiled as several parts in parallel (one per
 group of template instantiations), the GF(2)[t] kernels, the Von Neumann kernels
@@ -12,10 +12,11 @@ import subprocess
 import sys
 import sysconfig
 
+from ._lib import MARSHAL_PATH
+
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libextractor.so")
-MARSHAL = os.path.join(HERE, "_marshal.so")
 BUILD = os.path.join(HERE, "_build")
 ARCH = os.environ.get("EXT_OFFLOAD_ARCH", "gfx950")
 
@@ -41,37 +42,49 @@ def _run(cmd):
     return out
 
 
-def _marshal_job():
-    """The Python module that fills a batch's job array (host code only, against torch)."""
+def _build_marshal():
+    """The Python module that fills a batch's job array (host code only, against torch). The
+    binding does without it where it cannot be built."""
+    tmp = MARSHAL_PATH + ".tmp%d" % os.getpid()
+    try:
+        _run(_marshal_command(tmp))
+        os.replace(tmp, MARSHAL_PATH)
+    except (ImportError, OSError, RuntimeError) as e:
+        if os.path.exists(MARSHAL_PATH):  # (one of older sources)
+            os.remove(MARSHAL_PATH)
+        print("not built, batches are filled in Python: %s\n%s" % (MARSHAL_PATH, e), file=sys.stderr)
+
+
+def _marshal_command(out):
     import torch
     root = os.path.dirname(torch.__file__)
-    tmp = MARSHAL + ".tmp%d" % os.getpid()
-    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC",
-           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch.compiled_with_cxx11_abi(),
-           "-I" + sysconfig.get_paths()["include"], "-I" + os.path.join(root, "include"),
-           "-I" + os.path.join(root, "include", "torch", "csrc", "api", "include"),
-           os.path.join(CSRC, "marshal.cpp"), "-o", tmp, "-L" + os.path.join(root, "lib"), "-ltorch_python",
-           "-ltorch_cpu", "-lc10"]
-    return cmd, tmp
+    return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC",
+            "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch.compiled_with_cxx11_abi(),
+            "-DTORCH_BUILT_WITH=\"%s\"" % torch.__version__,
+            "-I" + sysconfig.get_paths()["include"], "-I" + os.path.join(root, "include"),
+            "-I" + os.path.join(root, "include", "torch", "csrc", "api", "include"),
+            os.path.join(CSRC, "marshal.cpp"), "-o", out, "-L" + os.path.join(root, "lib"), "-ltorch_python",
+            "-ltorch_cpu", "-lc10"]
 
 
 def build(verbose: bool = False) -> str:
     os.makedirs(BUILD, exist_ok=True)
-    jobs = [_marshal_job()]
+    jobs = []
     for part in range(NTT_PARTS):
         obj = os.path.join(BUILD, "ntt_part%d.o" % part)
         jobs.append(([HIPCC] + FLAGS + ["-DNTT_PART=%d" % part, "-c", os.path.join(CSRC, "ntt.hip"), "-o", obj], obj))
     for src, extra in (("vonneumann.hip", VN_FLAGS), ("gf2.hip", []), ("abi.cpp", [])):
         obj = os.path.join(BUILD, os.path.splitext(src)[0] + ".o")
         jobs.append(([HIPCC] + FLAGS + extra + ["-c", os.path.join(CSRC, src), "-o", obj], obj))
-    workers = min(len(jobs), max(1, (os.cpu_count() or 2)))
+    workers = min(len(jobs) + 1, max(1, (os.cpu_count() or 2)))
     with cf.ThreadPoolExecutor(workers) as ex:
+        marshal = ex.submit(_build_marshal)
         for out in ex.map(lambda j: _run(j[0]), jobs):
             if verbose and out.strip():
                 print(out)
-    os.replace(jobs[0][1], MARSHAL)
+        marshal.result()
     tmp = OUT + ".tmp%d" % os.getpid()
-    _run([HIPCC, "--offload-arch=" + ARCH, "-shared", "-o", tmp] + [j[1] for j in jobs[1:]])
+    _run([HIPCC, "--offload-arch=" + ARCH, "-shared", "-o", tmp] + [j[1] for j in jobs])
     os.replace(tmp, OUT)
     return OUT
 

@@ -129,5 +129,7 @@ PyMODINIT_FUNC PyInit__marshal(void) {
                  {&kinds[EXT_KIND_DODIS], "dodis"}};
     for (auto &e : names)
         if (!(*e.at = PyUnicode_InternFromString(e.text))) return nullptr;
-    return PyModule_Create(&module);
+    PyObject *mod = PyModule_Create(&module);
+    if (mod && PyModule_AddStringConstant(mod, "torch", TORCH_BUILT_WITH) != 0) Py_CLEAR(mod);
+    return mod;
 }
