@@ -605,12 +605,14 @@ uint64_t vn_pair_tiles(uint64_t n) { return (vn_input(n).nwords + VP_TILE_W - 1)
 
 uint64_t vn_tiles(uint64_t n) { return (vn_input(n).nwords + VN_TILE_W - 1) / VN_TILE_W; }
 
+// room for either form: the one pass has three words a tile and its counters, the two passes
+// 12 bytes for each of their (smaller) tiles
 size_t vn_workspace_bytes(uint64_t n) {
-    const uint64_t T = vn_tiles(n);
-    return (size_t)(3 * T * 8 + 256);
+    const uint64_t pairs = vn_two_pass(n) ? vn_pair_tiles(n) * (sizeof(uint64_t) + sizeof(uint32_t)) : 0;
+    const uint64_t one = 3 * vn_tiles(n) * 8;
+    return (size_t)((one > pairs ? one : pairs) + 256);
 }
 
-// (12 bytes for each of the at most twice as many tiles: within vn_workspace_bytes)
 VnPairWork vn_pair_work(char *ws, uint64_t n) {
     VnPairWork w;
     w.head = (uint64_t *)ws;
