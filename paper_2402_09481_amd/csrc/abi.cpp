@@ -511,6 +511,7 @@ struct ext_ctx {
     // extractions run the number-theoretic transform of that plan
     std::map<int, int> chosen;
     bool gf2 = true;  // the GF(2)[t] path (off where a testing aid forces a transform)
+    bool vn_one_pass = false;  // testing aid: the one-pass Von Neumann form for every length
     // pinned status words for EXT_SYNC calls without a status pointer
     std::vector<int32_t *> pinned_status;
     // batch graph cache
@@ -1165,7 +1166,7 @@ hipError_t enqueue_vn(ext_ctx *c, const uint64_t *x, uint64_t n, uint64_t *z, ui
     Tracer tr(c, s, false);
     LaunchEvent *done = lease_event(lease, s);
     hipError_t e;
-    if (vn_two_pass(n)) {
+    if (vn_two_pass(n) && !c->vn_one_pass) {
         const VnPairWork w = vn_pair_work(lease.ptr, n);
         tr.begin();
         e = launch_vn_count(x, n, w, s);
@@ -1504,6 +1505,7 @@ int ext_create(ext_ctx **out, int hip_device, size_t hbm_budget_bytes, const cha
     c->batch_split_min_lg = BATCH_SPLIT_MIN_LG;
     if (const char *v = getenv("EXT_SPLIT_MIN_LG")) c->split_min_lg = atoi(v);
     if (const char *v = getenv("EXT_BATCH_SPLIT_MIN_LG")) c->batch_split_min_lg = atoi(v);
+    c->vn_one_pass = getenv("EXT_VN_ONE_PASS") != nullptr;
     // (a context that a testing aid shapes runs the transform it asks for)
     c->gf2 = !ff && !c->piece_bits && !getenv("EXT_SPLIT_MIN_LG") && !getenv("EXT_BATCH_SPLIT_MIN_LG");
     // twiddle tables
