@@ -15,6 +15,8 @@ namespace {
 constexpr size_t GUARD = size_t(1) << 16;
 std::map<char *, size_t> g_blocks;
 int g_faults = 0;
+bool g_running = false, g_capturing = false;  // what the model answers
+int g_unfenced = 0, g_events = 0;             // events made, and those without a system fence
 
 void *block_new(size_t bytes) {
     char *p = (char *)calloc(1, bytes + GUARD);
@@ -187,10 +189,21 @@ hipError_t hipMemcpyAsync(void *to, const void *from, size_t bytes, hipMemcpyKin
     memcpy(to, from, bytes);
     return hipSuccess;
 }
-hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { return *e = (hipEvent_t)1, hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned flags) {
+    ++g_events;
+    g_unfenced += (flags & hipEventDisableSystemFence) != 0;
+    return *e = (hipEvent_t)1, hipSuccess;
+}
 hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
-hipError_t hipEventQuery(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventQuery(hipEvent_t) {
+    g_faults += g_capturing;
+    return g_running ? hipErrorNotReady : hipSuccess;
+}
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *s) {
+    *s = g_capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+    return hipSuccess;
+}
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
 hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
@@ -222,6 +235,23 @@ void host_ctx_free(void *p) {
     for (auto &b : c->free_blocks) block_free(b.ptr);
     pinned_release_all(c);
     delete c;
+}
+
+// a workspace taken and given back, its last call still running or not, the stream captured or
+// not; returns 1 if the release's event has no system fence (-1: a query under capture)
+int host_release_event(void *ctx, int running, int capturing) {
+    ext_ctx *c = (ext_ctx *)ctx;
+    g_running = running;
+    g_capturing = capturing;
+    g_faults = g_unfenced = g_events = 0;
+    Lease l;
+    const int rc = pool_acquire(c, 1 << 20, nullptr, l);
+    LaunchEvent *done = lease_event(l);
+    const bool carried = done && done->ev;
+    pool_release(c, l, nullptr);
+    g_running = g_capturing = false;
+    if (rc != EXT_OK || g_faults || g_events != 1 || carried != (g_unfenced == 1)) return -1;
+    return g_unfenced;
 }
 
 // One batch; shapes: kind, n, m of every job. Returns extract_batch's code. *faults: launches

@@ -154,3 +154,12 @@ def test_few_members_of_one_length_share_a_transform(lib, context, jobs, transfo
     short = sum(n + m - 1 <= 1 << 14 for n, m in jobs)
     assert ("strided" in r.labels, "fwd" in r.labels) == (transform, not transform), r.labels
     assert r.done == (short if transform else len(jobs))
+
+
+def test_the_event_behind_a_workspace(lib, context):
+    """An event without a system fence, carried by the last launch, only where the workspace's last
+    call is still running: a call that comes after a wait records an ordinary one."""
+    c = context()
+    lib.host_release_event.argtypes = [ctypes.c_void_p, ctypes.c_int, ctypes.c_int]
+    got = [lib.host_release_event(c, *s) for s in ((0, 0), (0, 0), (1, 0), (1, 0), (0, 0), (1, 1), (0, 1), (1, 0))]
+    assert got == [0, 0, 1, 1, 0, 0, 0, 1]
