@@ -1297,8 +1297,7 @@ __device__ __forceinline__ void row_round(u32 *v, u32 wave_row, u32 lane_row, u3
             u32 x = one & plus_one;
             unroll<HI + 1, ROWS_LG_MAX>([&](auto j) {
                 constexpr u32 c = forms81(TW(I, j)).w[h];
-                if (j >= 8) x ^= (u32)__builtin_amdgcn_sbfe((int)wave_row, j, 1) & c;
-                else if (LANES) x ^= bit_mask<j>(lane_row) & c;
+                if (LANES && j < 8) x ^= bit_mask<j>(lane_row) & c;
                 else x ^= (u32)__builtin_amdgcn_sbfe((int)wave_row, j, 1) & c;
             });
             f.w[h] = x;
@@ -1497,14 +1496,7 @@ __device__ __forceinline__ void rows_stages(u32 *v, u32 *lds, u32 plus_one) {
     const u32 wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     auto sync = [](u32 *) { __syncthreads(); };
     // register row bits (HI, HI - 1) in rounds 11/10, 9/8, 7/6, 5/4, 3/2, 1/0; an odd P starts
-    // with the upper bit alone
-    constexpr int TOP = (P & 1) ? P : P - 1;  // HI of the first round
-    auto top_round = [&](auto hi_) {
-        constexpr int HI = hi_;
-        // (the first round has no row bits above it)
-        row_round<HI, INV, true, !(P & 1), false>(v, 0u, 0u, plus_one);
-    };
-    (void)top_round;
+    // with the upper bit alone (the first round has no row bits above it)
     auto ex = [&](auto from, auto to) {
         rows_exchange<P>(v, lds, [](int b) { return row_at<P, decltype(from)::value>(b); },
                          [](int b) { return row_at<P, decltype(to)::value>(b); }, sync);
@@ -1522,7 +1514,7 @@ __device__ __forceinline__ void rows_stages(u32 *v, u32 *lds, u32 plus_one) {
     auto r5 = [&] { row_round<5, INV, true, true, true>(v, wave << 8, lane << 2, plus_one); };
     auto r3 = [&] { row_round<3, INV, true, true, true>(v, wave << 8, lane << 2, plus_one); };
     auto r1 = [&] { row_round<1, INV, true, true, true>(v, wave << 8, lane << 2, plus_one); };
-    static_assert(P >= 8 && P <= 12 && TOP >= 7, "rows");
+    static_assert(P >= ROWS_LG_MIN && P <= ROWS_LG_MAX, "rows");
     if constexpr (!INV) {
         if constexpr (P == 12) {
             r11();
