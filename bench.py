@@ -346,7 +346,7 @@ def run_headline(args):
     rv = out["roofline"]["valu"]
     out["roofline"]["binding"] = "valu" if rv is not None and rv["frac"] > out["roofline"]["frac"] else "hbm"
     if args.warm:
-        # NEXT row f1: the same extraction with the seed's transform cached (a hit
+        # the same extraction with the seed's transform cached (a hit
         # skips one of the three transforms; 7 L w algorithmic bytes)
         ctx.extract("toeplitz", x, y, job.n, job.m, z=z, stream=stream, cache_seed=True, single_transform=True)
         torch.cuda.synchronize()
@@ -364,19 +364,20 @@ def run_headline(args):
                                    "achieved_GBs": round(wbytes / (wms * 1e-3) / 1e9, 1)}
         ctx.seed_cache_clear()
     if args.two_piece:
-        out["two_piece"] = run_two_piece(ctx, job, x, y, z, stream, args, ms)
+        out["default_route"] = run_default_route(ctx, job, x, y, z, stream, args, ms)
     ctx.close()
     del x, y, z
     torch.cuda.empty_cache()
     return out, job, z_head
 
 
-def run_two_piece(ctx, job, x, y, z, stream, args, single_ms):
-    """NEXT row f2: the same extraction by the library's default route for this shape
-    (products over GF(2)[t] by additive FFTs in bit planes; a tuned plan keeps the two-piece
-    schedule over 3*2^30+1). Same output bits (checked here against the single transform); a
-    different arithmetic path, so it is reported beside the headline, not as it. The bit-plane
-    kernels carry no algorithmic bytes: instructions bound them."""
+def run_default_route(ctx, job, x, y, z, stream, args, single_ms):
+    """The headline's extraction by the library's default route for its shape (products over
+    GF(2)[t] by additive FFTs in bit planes). Same output bits (checked here against the
+    single transform); a different arithmetic path, so it is reported beside the headline,
+    not as it. The kernels that ran are named; where they are a transform's (a plan set by
+    the caller, a testing aid), with its algorithmic bytes. The bit-plane kernels have none:
+    instructions bound them."""
     import torch
     z1 = z.clone()
     ctx.extract("toeplitz", x, y, job.n, job.m, z=z, stream=stream)
@@ -391,31 +392,36 @@ def run_two_piece(ctx, job, x, y, z, stream, args, single_ms):
     torch.cuda.synchronize()
     ctx.profile(False)
     ms = e0.elapsed_time(e1) / args.steps
-    L, w = 1 << 30, 4
-    a = job.n // 2
     agg = {}
     for label, t in ctx.profile_read():
         e = agg.setdefault(label, [0.0, 0])
         e[0] += t
         e[1] += 1
+    out = {"ms_per_step": round(ms, 3), "value": round(job.m / (ms * 1e-3) / 1e6, 2), "unit": "Mbit/s",
+           "speedup_vs_single_transform": round(single_ms / ms, 2), "same_bits_as_single_transform": same}
+    planes = any(label.startswith("gf2") for label in agg)
+    out["route"] = "gf2" if planes else "two pieces"
     kernels, total_bytes = [], 0
+    L, w, a = 1 << 30, 4, job.n // 2
     for label, (tot, cnt) in agg.items():
-        b = kernel_bytes(label, L, w, a, a + job.m - 1, job.m) if "[" in label or not label.startswith("gf2") else 0
-        total_bytes += b * cnt // args.steps
-        kernels.append({"kernel": label, "launches_per_step": cnt // args.steps, "avg_ms": round(tot / cnt, 4),
-                        "algo_bytes": b, "achieved_GBs": round(b / (tot / cnt * 1e-3) / 1e9, 1)})
+        k = {"kernel": label, "launches_per_step": cnt // args.steps, "avg_ms": round(tot / cnt, 4)}
+        if not planes:
+            b = kernel_bytes(label, L, w, a, a + job.m - 1, job.m)
+            total_bytes += b * cnt // args.steps
+            k.update(algo_bytes=b, achieved_GBs=round(b / (tot / cnt * 1e-3) / 1e9, 1))
+        kernels.append(k)
     kernels.sort(key=lambda k: -k["avg_ms"] * k["launches_per_step"])
-    return {"ms_per_step": round(ms, 3), "value": round(job.m / (ms * 1e-3) / 1e6, 2), "unit": "Mbit/s",
-            "speedup_vs_single_transform": round(single_ms / ms, 2), "same_bits_as_single_transform": same,
-            "transform_length": L, "word_bytes": w, "algo_bytes_per_step": total_bytes,
-            "achieved_GBs": round(total_bytes / (ms * 1e-3) / 1e9, 1), "kernels": kernels}
+    if not planes:
+        out.update(transform_length=L, word_bytes=w, algo_bytes_per_step=total_bytes,
+                   achieved_GBs=round(total_bytes / (ms * 1e-3) / 1e9, 1))
+    out["kernels"] = kernels
+    return out
 
 
 def run_batched(log, count=4096, reps=10, per_block=True):
     """The batched workload (4096 Toeplitz/Circulant blocks, n log-uniform in
-    [2^10, 2^22], m = n/2): extract_batch (one persistent launch for the
-    single-workgroup sizes plus grouped multi-pass launches, replayed from a HIP
-    graph) against one extraction call sequence per block, same jobs, same GPU.
+    [2^10, 2^22], m = n/2): extract_batch (the launches that all blocks share,
+    replayed from a HIP graph) against one extraction call sequence per block, same jobs, same GPU.
     Returns the summary, the jobs and the batched outputs (host copies)."""
     import numpy as np
     import torch
@@ -505,10 +511,7 @@ def cpu_baseline_batched(jobs, zs, blocks=128, seed=5):
 
 def run_paper_shapes(log, reps=2):
     """The paper's QKD privacy-amplification shapes and QRNG randomness-extraction
-    shapes (NEXT row f3): QKD as two pieces of 2^30 over 3*2^30+1, QRNG (n = 6.5e9)
-    as the piece schedule over the 64-bit field with transforms of 2^31."""
-    import ctypes
-
+    shapes (n = 6.5e9), on the default route."""
     import numpy as np
     import torch
 
@@ -547,12 +550,9 @@ def run_paper_shapes(log, reps=2):
         e1.record()
         torch.cuda.synchronize()
         ms = e0.elapsed_time(e1) / reps
-        wb = ctypes.c_int32()
-        L = int(ctx._lib.ext_plan_length(P.KINDS[kind], n, m, ctypes.byref(wb)))
         out[name] = {"kind": kind, "n": n, "m": m, "ms": round(ms, 3),
                      "output_Mbit_s": round(m / (ms * 1e-3) / 1e6, 2),
-                     "input_Mbit_s": round(n / (ms * 1e-3) / 1e6, 2),
-                     "transform_length": L, "word_bits": wb.value}
+                     "input_Mbit_s": round(n / (ms * 1e-3) / 1e6, 2)}
         del x, y, z
         ctx.trim()
         torch.cuda.empty_cache()
@@ -562,7 +562,7 @@ def run_paper_shapes(log, reps=2):
 
 
 def run_von_neumann(log, reps=10, oracle_bits=1 << 27):
-    """The Von Neumann extractor (NEXT row f4(b)): i.i.d. input with min-entropy half
+    """The Von Neumann extractor: i.i.d. input with min-entropy half
     its length (the paper's throughput-figure setting), at the figure's largest input
     length and at 2^33 bits. Input and output bytes against the HBM roofline; the
     oracle timed on a sample for context."""
@@ -704,7 +704,7 @@ def main():
     ap.add_argument("--paper-shapes", action="store_true", help="also time the paper's QKD extraction shapes")
     ap.add_argument("--von-neumann", action="store_true", help="also time the Von Neumann extractor")
     ap.add_argument("--two-piece", action="store_true",
-                    help="also time the headline shape with the default two-piece plan")
+                    help="also time the headline's shape on the default route")
     ap.add_argument("--no-small", action="store_true",
                     help="skip the small Toeplitz latency and Dodis timing (run by default, about a second)")
     ap.add_argument("--copy-calibration-gib", type=float, default=0.0,

@@ -59,9 +59,9 @@ static_assert(VN_WPT >= 2 && VN_WPT <= 32, "words per thread");
 static_assert(VN_NT >= 256 && VN_NT <= 1024 && VN_NT % 64 == 0, "the byte table is filled by the first 256 threads");
 
 // Two passes up to here: the second pass reads the input from the 256 MB last-level
-// cache as long as it is kept there. One pass against two, us: n = 10^6 14.3 / 9.1,
-// 2^27 19.0 / 12.8, 5*10^8 40.9 / 30.3, 2^30 68.2 / 56.2, 3*2^29 87.7 / 80.0,
-// 2^31 121 / 121, 3*2^30 172 / 213.
+// cache as long as it is kept there. One pass against two, us a call back to back: n =
+// 10^6 15.5 / 10.2, 2^27 19.6 / 11.9, 5*10^8 41.6 / 30.6, 2^30 65.3 / 55.3, 3*2^29 89.2 /
+// 80.5, 2^31 122 / 121, 3*2^30 174 / 213.
 constexpr uint64_t VN_TWO_MAX = 3ull << 29;
 constexpr uint64_t ST_AGG = 1ull << 62, ST_PREFIX = 2ull << 62, ST_ERR = 3ull << 62;
 constexpr uint64_t ST_VAL = (1ull << 62) - 1;
@@ -398,9 +398,9 @@ __global__ void k_vn_fix(VnWork w, uint64_t T, uint64_t *__restrict__ z, uint64_
 // tiles after it. (Where tiles met in the workspace by atomics instead, with the counts
 // in the same lines, that took 17 us.) A thread's eight words are loaded from where they
 // are (64 bytes a lane: the second half of a line comes from the L1), not staged through
-// LDS. At n = 5*10^8 (62.5 MB in, half of the pairs kept) the call went from 43.6 to
-// 30.1 us: the count 11 us, the cache's 6 TB/s; the packing 19 us, of which 6.5 go to the
-// byte table's reads and shifts and the rest to loads and stores over two rounds of
+// LDS. At n = 5*10^8 (62.5 MB in, 41% of the pairs kept) the call takes 30.6 us, and 41.6
+// in one pass: the count 11 us, the cache's 6 TB/s; the packing 19 us, of which 6.5 go to
+// the byte table's reads and shifts and the rest to loads and stores over two rounds of
 // workgroups that are not full. Tiles of 256 threads x 16 words or 1024 x 4: 3 and 5 us
 // more.
 constexpr int VP_NT = 512;
