@@ -985,8 +985,10 @@ __device__ inline void degen_part(const Gf2Job &J, u32 g, u32 *red) {
 // after those run the Dodis check. tab: per workgroup its job and its number within
 // the job (nullptr: the one job). Bound by instruction issue: 5361 instructions a wave of
 // two rows, 17.8 us where each SIMD has one wave (a lone wave issues one in 7 clocks: n =
-// 2^20) and 660 us for the 163839 rows of n = 2^30, m = 2^29. 113 registers hold four
-// waves a SIMD; five or six waves spill 59 or 125 registers.
+// 2^20) and 660 us for the 163839 rows of n = 2^30, m = 2^29, 98% of what their mix can
+// issue (3.6 clocks each: shifts, masks, moves between lanes and operands in scalar
+// registers take four, swaps between lanes eight, the rest two and a half). 113 registers
+// hold four waves a SIMD; five or six waves spill 59 or 125 registers.
 __global__ void __launch_bounds__(64 * FWD_WAVES) __attribute__((amdgpu_waves_per_eu(4))) k_gf2_fwd(const Gf2Job *jobs, Gf2Job one, const uint2 *tab) {
     __shared__ __align__(16) u32 lds_all[FWD_WAVES * 2 * ROW_LDS];
     const uint2 tw = tab ? tab[blockIdx.x] : make_uint2(0, blockIdx.x);
@@ -1614,8 +1616,8 @@ __device__ __forceinline__ void store_unit(u32 *p, const u32 *x) {
 // Forward: workgroup = slice of a group of X (its hx rows, zeros above) or of a window of
 // S (its hx + hz - 1 rows, at the top of the 2^P). With P = 12 one workgroup fills a CU's
 // registers and LDS: 5056 workgroups (n = 2^30, m = 2^29) take 1170 us, 59 us a round,
-// of which the 7150 instructions a wave are 30 and the 256 KB in and out the rest, not
-// overlapped. The larger P is still the cheaper: half of it would double the sums of
+// of which the 7150 instructions a wave (3.1 clocks each) are 40 and the 256 KB in and out
+// the rest, hardly overlapped. The larger P is still the cheaper: half of it would double the sums of
 // products.
 template <int P>
 __global__ void __launch_bounds__(Rows<P>::NT) __attribute__((amdgpu_waves_per_eu(P == 12 ? 4 : 1)))
@@ -1681,7 +1683,7 @@ k_gf2_rows_fwd(const Gf2Job *jobs, Gf2Job one, const uint2 *tab) {
 // in 2 each) and no operand ahead of its use, so the next input group's row and window
 // come straight into LDS while this one's products run. n = 2^30, m = 2^29 (32 groups by
 // 16): 1250 -> 640 us, of which the layout of the rows gave 120, the loads ahead 150 and
-// the second wave 340; the instructions alone are 380 us. Two turns ahead: 1005 against
+// the second wave 340; the instructions alone are 450 us (2.5 clocks each). Two turns ahead: 1005 against
 // 978 us before the second wave. TG = 1 (one group of z) reads 64 bytes for every product
 // and runs at 4.2 TB/s.
 template <int TG>

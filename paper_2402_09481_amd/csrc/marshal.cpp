@@ -2,7 +2,7 @@
 // What the binding's Python loop does (Context.batch), for jobs of the ordinary form;
 // fill() returns False at the first job of any other form (other types, a tensor off the GPU,
 // too short or not contiguous, ...), and the Python loop then handles the whole batch and
-// raises what it has to. Measured on 4096 jobs: 9.7 ms in Python.
+// raises what it has to. 4096 jobs: 0.22 ms, 9.8 ms in the Python loop.
 #include <Python.h>
 
 #include <ATen/core/Tensor.h>
