@@ -77,8 +77,11 @@ extern "C" {
  * at that address while they are cached (ext_seed_cache_clear drops them).
  * A hit skips one of the three transforms. The flag keeps the number-theoretic
  * transform where the default would be products over GF(2)[t] (see
- * EXT_SINGLE_TRANSFORM). Sizes that run in one workgroup and the piece schedules
- * ignore the flag. */
+ * EXT_SINGLE_TRANSFORM), which are faster than a hit for most shapes: it pays beside
+ * EXT_SINGLE_TRANSFORM or a plan that the caller has set, and hardly otherwise (MI355X,
+ * m = n / 2, us a call by default / on a hit: n = 2^16 13 / 27, 2^19 36 / 34, 2^20 40 / 44,
+ * 2^24 116 / 316, 2^28 660 / 6100). Sizes that run in one workgroup and the piece
+ * schedules ignore the flag (n = 2^30: 2.8 ms by default, 33 ms in two pieces). */
 #define EXT_SEED_CACHED 8u
 /* Single calls: compute the extraction as one number-theoretic transform.
  * By default most extractions are products over GF(2)[t] (bits in, bits out: short
@@ -206,7 +209,9 @@ typedef struct ext_job {
 
 /* Run many independent extractions (the paper's many privacy-amplification
  * blocks, section "Cryptomite for privacy amplification in QKD") as a few
- * grouped launches. Jobs on the GF(2)[t] route share its launches; the others are
+ * grouped launches. Jobs on the GF(2)[t] route share its launches (two to eight of one
+ * transform length, 2^20 coefficients together at most, share a transform's instead, and
+ * so does a batch whose descriptors would not fit the budget otherwise); the others are
  * grouped by transform size: all single-workgroup
  * sizes (transform length <= 2^14) run in one persistent launch that takes
  * jobs from a work counter, larger sizes as batched multi-pass launches, one

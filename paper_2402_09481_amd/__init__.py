@@ -158,8 +158,11 @@ class Context:
                 status=None, stream=None, check: bool = True, cache_seed: bool = False,
                 single_transform: bool = False, no_alloc: bool = False) -> "object":
         """cache_seed: keep / reuse the seed's transform (the seed bits at y must not
-        change while cached; see seed_cache_clear). single_transform: no two-piece
-        split (one transform: over the 64-bit field beyond 2^30, over 15*2^27+1 at 2^27).
+        change while cached; see seed_cache_clear). It keeps the number-theoretic transform,
+        which the default route beats even on a hit for most sizes (m = n/2: n = 2^16 13 us by
+        default, 27 on a hit; 2^19 36, 34; 2^24 116, 316; 2^28 0.66 ms, 6.1 ms): of use beside
+        single_transform. single_transform: one number-theoretic transform (over the 64-bit
+        field beyond 2^30, over 15*2^27+1 at 2^27).
         no_alloc: Toeplitz through extract_toeplitz_noalloc (the library's fixed
         per-GPU workspace; calls on one GPU must not overlap)."""
         import torch
