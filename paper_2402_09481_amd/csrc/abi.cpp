@@ -858,9 +858,9 @@ bool still_running(hipEvent_t ev, hipStream_t stream) {
         (void)hipGetLastError();
         return false;
     }
-    if (hipEventQuery(ev) == hipSuccess) return false;
-    (void)hipGetLastError();  // (not ready is no error of a later call)
-    return true;
+    const hipError_t e = hipEventQuery(ev);
+    if (e != hipSuccess) (void)hipGetLastError();  // (not ready is no error of a later call)
+    return e == hipErrorNotReady;
 }
 
 // Take a block of at least `size` bytes usable on `stream`.

@@ -15,7 +15,8 @@ namespace {
 constexpr size_t GUARD = size_t(1) << 16;
 std::map<char *, size_t> g_blocks;
 int g_faults = 0;
-bool g_running = false, g_capturing = false;  // what the model answers
+int g_running = 0;  // what an event query answers: 0 done, 1 not ready, 2 an error
+bool g_capturing = false;
 int g_unfenced = 0, g_events = 0;             // events made, and those without a system fence
 
 void *block_new(size_t bytes) {
@@ -198,7 +199,7 @@ hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
 hipError_t hipEventQuery(hipEvent_t) {
     g_faults += g_capturing;
-    return g_running ? hipErrorNotReady : hipSuccess;
+    return g_running == 2 ? hipErrorInvalidHandle : g_running ? hipErrorNotReady : hipSuccess;
 }
 hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *s) {
     *s = g_capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
@@ -237,7 +238,7 @@ void host_ctx_free(void *p) {
     delete c;
 }
 
-// a workspace taken and given back, its last call still running or not, the stream captured or
+// a workspace taken and given back, its last call done, still running or unknown (0, 1, 2), the stream captured or
 // not; returns 1 if the release's event has no system fence (-1: a query under capture)
 int host_release_event(void *ctx, int running, int capturing) {
     ext_ctx *c = (ext_ctx *)ctx;
@@ -249,7 +250,8 @@ int host_release_event(void *ctx, int running, int capturing) {
     LaunchEvent *done = lease_event(l);
     const bool carried = done && done->ev;
     pool_release(c, l, nullptr);
-    g_running = g_capturing = false;
+    g_running = 0;
+    g_capturing = false;
     if (rc != EXT_OK || g_faults || g_events != 1 || carried != (g_unfenced == 1)) return -1;
     return g_unfenced;
 }
