@@ -65,7 +65,7 @@ extern "C" {
 /* Wait for the stream and return the device status. */
 #define EXT_SYNC 2u
 /* extract_batch only: record the batch's launch sequence as a HIP graph on
- * first use of a batch signature (the multiset of transform sizes) and replay it
+ * first use of a batch signature (the sizes of all its launches) and replay it
  * afterwards. Worth it when the same signature repeats; without the flag the
  * grouped launches are enqueued directly. The graph is built node by node, not
  * by stream capture, so other host threads may use the device meanwhile. */
